@@ -11,13 +11,13 @@
 //   * quadrature in u = ln t, composite 20-point Gauss-Legendre (width-4 panels on
 //     [-40,-8], width-1.5 panels on [-8, ln T*]), T* = 8 R^2 + 64 so that every factor's
 //     asymptotic series has ratio <= 1/32 beyond T*;
-//   * one thread per quadrature node computes It_n(2 t_q), n = 0..R, by the backward
-//     recurrence of the ratios r_n = I_n / I_{n-1} = x / (2n + x r_{n+1}) (Miller's method in
-//     ratio form, no overflow), normalised by It_0 + 2 sum_{n>=1} It_n = 1;
-//   * one thread per table entry forms the separable sum sum_q W_q B_q[a] B_q[b] B_q[c]
-//     (B stored node-major so consecutive a are coalesced) plus the tail series.
+//   * B[n][q] = It_n(2 t_q), n = 0..R (nodes fastest, padded to whole steps of kStep with
+//     zeros), by one of three forms without a division chain (bessel_kernel);
+//   * the separable sum sum_q W_q B_a B_b B_c as FP64 matrix products, one per c (table_kernel),
+//     with the tail series as its last steps.
 // Table layout: sorted triple a <= b <= c at index c(c+1)(c+2)/6 + b(b+1)/2 + a (the
 // 1/48 symmetry of Sec. 4).
+#include <algorithm>
 #include <array>
 #include <cmath>
 #include <mutex>
@@ -30,6 +30,7 @@ namespace {
 
 constexpr int kGL = 20;          // Gauss-Legendre points per panel
 constexpr int kTail = 10;        // asymptotic terms per Bessel factor
+constexpr int kStep = 8;         // quadrature nodes of one unrolled step of the table's products
 constexpr double kULo = -40.0;
 
 // Gauss-Legendre nodes/weights on [-1, 1] by Newton iteration on P_n.
@@ -77,9 +78,7 @@ struct Rule {
 };
 
 // Node q of the rule: t_q = e^u and the weight of dt = t du with the factor e^{-s t}.
-__global__ void nodes_kernel(const Rule rule, int Q, double* __restrict__ t, double* __restrict__ w) {
-    const int q = blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= Q) return;
+__device__ inline void node(const Rule& rule, int q, double* t, double* w) {
     const int p = q / kGL, i = q % kGL;
     double lo, hi;
     if (p < rule.n_lo) {
@@ -92,8 +91,8 @@ __global__ void nodes_kernel(const Rule rule, int Q, double* __restrict__ t, dou
     }
     const double u = 0.5 * (hi - lo) * rule.gx[i] + 0.5 * (hi + lo);
     const double tq = exp(u);
-    t[q] = tq;
-    w[q] = 0.5 * (hi - lo) * rule.gw[i] * tq * exp(-rule.s * tq);
+    *t = tq;
+    *w = 0.5 * (hi - lo) * rule.gw[i] * tq * exp(-rule.s * tq);
 }
 
 // int_T^inf exp(-s t) t^{-3/2-k} dt for k = 0..kmax (host).
@@ -113,23 +112,140 @@ void tail_moments(double s, double T, int kmax, double* J) {
     }
 }
 
-__global__ void bessel_kernel(const double* __restrict__ t, int Q, int R, double* __restrict__ B) {
-    const int q = blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= Q) return;
-    const double x = 2.0 * t[q];
-    double* row = B + (int64_t)q * (R + 1);
-    const int nstart = R + 60 + (int)(10.0 * sqrt(x));
-    double r = 0.0, S = 0.0;
-    for (int n = nstart; n >= 1; --n) {
-        r = x / (2.0 * n + x * r);
-        S = r * (1.0 + S);
-        if (n <= R) row[n] = r;
+// It_n(x) at the nodes x = 2 t_q, by the size of x:
+//   x < 2^-20       the ratio I_n / I_{n-1} = (x / 2n) (1 - x^2 / (4n (n + 1))) to FP64 rounding, multiplied up;
+//   x < hankel_x    Miller's recurrence I_{n-1} = I_{n+1} + (2n/x) I_n downward: one fused multiply-add
+//                   per step on the chain.  For x >= 100 it starts from the ratio
+//                   I_{N+1} / I_N = x / (N + 1/2 + sqrt((N + 3/2)^2 + x^2)) (to about 1e-4) at
+//                   (N - 60)^2 = R^2 + 28 x, which the recurrence contracts by at least e^{-28} on the
+//                   way to R, and is normalised by the series of It_0; below, from zero at
+//                   (N - 60)^2 = R^2 + 81 x, normalised by It_0 + 2 sum It_{2k} = (1 + e^{-2x}) / 2.
+//                   The values are scaled down by 2^-600 whenever they pass 2^300 (they grow by at most
+//                   2^272 per 8 steps for x >= 2^-20); a stored row knows by its index how many
+//                   scalings it has missed.  The node is in effect 2 / fl(2 / x): its weight follows,
+//                   so that the integrand's stationary point hides the difference;
+//   else            (x >= R^2 + 100) the large-argument series, whose terms fall at least like 1 / (2^k k!).
+// What bounds it: the chain of the largest recurrence, N = 5.4 R + 60 dependent steps on one wavefront per
+// 64 nodes: 46 us at R = 238.  In ratio form, each step an FP64 division, and with N = R + 60 + 10 sqrt(x) up
+// to x = 16 R^2, it took 857 us (227 us at R = 60).
+constexpr int kBesselThreads = 64;
+constexpr int kHankelTerms = 16;
+
+__device__ inline double bessel_large(int n, double x) {
+    const double mu = 4.0 * n * (double)n, r = 1.0 / (8.0 * x);
+    double term = 1.0, sum = 1.0;
+#pragma unroll
+    for (int k = 1; k <= kHankelTerms; ++k) {
+        term *= ((2.0 * k - 1.0) * (2.0 * k - 1.0) - mu) * r * (1.0 / k);
+        sum += term;
     }
-    double In = 1.0 / (1.0 + 2.0 * S);
-    row[0] = In;
-    for (int n = 1; n <= R; ++n) {
-        In *= row[n];
-        row[n] = In;
+    return sum / sqrt(2.0 * M_PI * x);
+}
+
+// Blocks [0, chain_blocks): one thread per node of [0, Qp); the rest: one thread per (row, node) of the
+// nodes [large_q0, Q) (those of them with x >= hankel_x).
+__global__ __launch_bounds__(kBesselThreads) void bessel_kernel(const Rule rule, int Q, int Qp, int R,
+                                                                int chain_blocks, int large_q0, double hankel_x,
+                                                                double* __restrict__ w, double* __restrict__ B) {
+    constexpr double kBig = 0x1p300, kDown = 0x1p-600;
+    double t, wq;
+    if ((int)blockIdx.x >= chain_blocks) {
+        const int64_t i = (int64_t)(blockIdx.x - chain_blocks) * kBesselThreads + threadIdx.x;
+        const int nq = Q - large_q0;
+        const int n = (int)(i / nq), q = large_q0 + (int)(i % nq);
+        if (n > R) return;
+        node(rule, q, &t, &wq);
+        if (2.0 * t >= hankel_x) B[(int64_t)n * Qp + q] = bessel_large(n, 2.0 * t);
+        return;
+    }
+    const int q = blockIdx.x * kBesselThreads + threadIdx.x;
+    if (q >= Qp) return;
+    double* col = B + q;
+    if (q >= Q) {   // padding of the last step
+        w[q] = 0.0;
+        for (int n = 0; n <= R; ++n) col[(int64_t)n * Qp] = 0.0;
+        return;
+    }
+    node(rule, q, &t, &wq);
+    w[q] = wq;
+    const double x = 2.0 * t;
+    if (x >= hankel_x) return;
+    if (x < 0x1p-20) {
+        const double x2 = x * x;
+        double In = exp(-x) * fma(0.25 * x2, fma(0.0625, x2, 1.0), 1.0);
+        col[0] = In;
+        double rn = 1.0;   // 1 / n
+        for (int n = 1; n <= R; ++n) {
+            const double rn1 = 1.0 / (n + 1.0);
+            In *= (0.5 * x * rn) * fma(-0.25 * x2, rn * rn1, 1.0);
+            rn = rn1;
+            col[(int64_t)n * Qp] = In;
+        }
+        return;
+    }
+    const double c = 2.0 / x;
+    w[q] = wq * fma(-rule.s * t, 0.5 * fma(-c, x, 2.0), 1.0);   // e^{-s t} at the node 2 / c
+    const bool large = x >= 100.0;
+    int n = 2 * ((int)(0.5 * sqrt(fma((double)R, (double)R, (large ? 28.0 : 81.0) * x))) + 30);   // even
+    double f = 0x1p-300, up = 0.0, even = 0.0;   // f_n, f_{n+1}, sum of f_{2k}, 2k > n
+    if (large) up = f * x / (n + 0.5 + sqrt(fma(n + 1.5, n + 1.5, x * x)));
+    // f_n -> f_{n-2}, f_{n-1} (n even)
+    auto pair = [&] {
+        const double nd = (double)n;
+        even += f;
+        up = fma(nd * c, f, up);
+        f = fma(fma(nd, c, -c), up, f);
+        n -= 2;
+    };
+    // rows past e1, e2, e3 have missed one, two, three scalings, and past e4 they are below 2^-1000
+    int e1 = 1 << 30, e2 = 1 << 30, e3 = 1 << 30, e4 = 1 << 30;
+    auto scale_down = [&] {
+        if (f > kBig) {
+            f *= kDown;
+            up *= kDown;
+            even *= kDown;
+            e4 = e3;
+            e3 = e2;
+            e2 = e1;
+            e1 = n;
+        }
+    };
+    while (n - 8 > R) {   // rows above R
+#pragma unroll
+        for (int k = 0; k < 4; ++k) pair();
+        scale_down();
+    }
+    while (n > 0 && (n > R || n % 8 != 0)) {   // down to a multiple of 8 in the table's range
+        if (n <= R) col[(int64_t)n * Qp] = f;
+        pair();
+        if (n + 1 <= R) col[(int64_t)(n + 1) * Qp] = up;
+        scale_down();
+    }
+    while (n > 0) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            col[(int64_t)n * Qp] = f;
+            pair();
+            col[(int64_t)(n + 1) * Qp] = up;
+        }
+        scale_down();
+    }
+    const double norm = large ? bessel_large(0, x) / f : 0.5 * (1.0 + exp(-2.0 * x)) / (f + 2.0 * even);
+    col[0] = f * norm;
+    constexpr int K = 24;   // loads in flight
+    for (int m0 = 1; m0 <= R; m0 += K) {
+        double v[K];
+#pragma unroll
+        for (int k = 0; k < K; ++k) v[k] = col[(int64_t)min(m0 + k, R) * Qp];
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const int m = m0 + k;
+            double y = v[k] * norm;
+            if (m > e1) y *= kDown;
+            if (m > e2) y *= kDown;
+            if (m > e3) y *= kDown;
+            if (m <= R) col[(int64_t)m * Qp] = m > e4 ? 0.0 : y;
+        }
     }
 }
 
@@ -143,38 +259,105 @@ __device__ inline void hankel(int n, double* a) {
     for (int k = 1; k <= kTail; ++k) a[k] = a[k - 1] * (-(mu - (2.0 * k - 1.0) * (2.0 * k - 1.0))) / (8.0 * k);
 }
 
-__global__ void table_kernel(const double* __restrict__ B, const double* __restrict__ W, int Q, int R,
-                             int64_t E, TailParams tp, double* __restrict__ out) {
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= E) return;
-    int64_t c = (int64_t)cbrt(6.0 * (double)e);
-    while (c > 0 && tetra(c) > e) --c;
-    while (tetra(c + 1) <= e) ++c;
-    const int64_t rem = e - tetra(c);
-    int64_t b = (int64_t)((sqrt(8.0 * (double)rem + 1.0) - 1.0) * 0.5);
-    while (b > 0 && b * (b + 1) / 2 > rem) --b;
-    while ((b + 1) * (b + 2) / 2 <= rem) ++b;
-    const int64_t a = rem - b * (b + 1) / 2;
+// Entries (a, b, c), a <= b <= c, of 16 x 16 tiles of (b, a) and CN values of c per wavefront:
+//   G(a, b, c) = sum_q (W_q B_b B_c)(q) B_a(q) + sum_i V_bc(i) alpha_i(a),
+//   V_bc(i) = sum_j alpha_j(b) U_c(i + j),  U_c(m) = sum_l alpha_l(c) J[m + l],
+// both sums contracted by v_mfma_f64_16x16x4 (A: the row's b, B: the column's a, so that a store is a run
+// of 16 consecutive entries).  A lane loads two nodes at a time: the order of the contraction is free.
+// What bounds it: the FP64 matrix cores (one product of 64 cycles per 64 triples and 4 nodes) and, at small
+// R, one wavefront's chain of products: 76 us at R = 238, where the products alone need 31.  One thread per
+// entry, with three loads per node and the 11^3 terms of the tail, took 1425 us (105 us at R = 60).
+constexpr int kTableWaves = 4;
+constexpr int kTile = 16;
 
-    double acc = 0.0;
-    const int ld = R + 1;
-    for (int q = 0; q < Q; ++q) {
-        const double* row = B + (int64_t)q * ld;
-        acc = fma(W[q] * row[a], row[b] * row[c], acc);
+template <int CN>
+__global__ __launch_bounds__(kTableWaves * 64) void table_kernel(const double* __restrict__ B,
+                                                                 const double* __restrict__ W, int Qp, int R,
+                                                                 const TailParams tp, double* __restrict__ out) {
+    using V4 = __attribute__((__vector_size__(4 * sizeof(double)))) double;
+    constexpr int kU = 2 * kTail + 2;   // U_c(m), m <= 2 kTail, and a zero
+    __shared__ double sJ[3 * kTail + 1], sU[kTableWaves][CN][kU], sA[kTableWaves][kTile][kTail + 2];
+    // the pair of tiles: y = tb (tb + 1) / 2 + ta, ta <= tb
+    const int y = blockIdx.y;
+    int tb = (int)((sqrtf(8.0f * (float)y + 1.0f) - 1.0f) * 0.5f);
+    while (tb * (tb + 1) / 2 > y) --tb;
+    while ((tb + 1) * (tb + 2) / 2 <= y) ++tb;
+    const int b0 = tb * kTile, a0 = (y - tb * (tb + 1) / 2) * kTile;
+    if (((int)blockIdx.x + 1) * CN * kTableWaves - 1 < b0) return;   // the block's every c is below b
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, row = lane & 15, kq = lane >> 4;
+    const int c0 = ((int)blockIdx.x * kTableWaves + wave) * CN;
+    if (threadIdx.x <= 3 * kTail) sJ[threadIdx.x] = tp.J[threadIdx.x];
+    const int a = min(a0 + row, R), b = min(b0 + row, R);
+    double h[kTail + 1];
+    hankel(a, h);
+    if (kq == 0) {
+        for (int i = 0; i <= kTail; ++i) sA[wave][row][i] = h[i];
+        sA[wave][row][kTail + 1] = 0.0;
     }
-    double ha[kTail + 1], hb[kTail + 1], hc[kTail + 1];
-    hankel((int)a, ha);
-    hankel((int)b, hb);
-    hankel((int)c, hc);
-    double tail = 0.0;
-    for (int i = 0; i <= kTail; ++i)
-        for (int j = 0; j <= kTail; ++j) {
-            const double aij = ha[i] * hb[j];
-            double s = 0.0;
-            for (int l = 0; l <= kTail; ++l) s = fma(hc[l], tp.J[i + j + l], s);
-            tail = fma(aij, s, tail);
+    __syncthreads();
+    for (int cn = 0; cn < CN; ++cn) {
+        hankel(min(c0 + cn, R), h);
+        if (lane < kU) {
+            double u = 0.0;
+            if (lane <= 2 * kTail)
+                for (int l = 0; l <= kTail; ++l) u = fma(h[l], sJ[lane + l], u);
+            sU[wave][cn][lane] = u;
         }
-    out[e] = acc + tail;
+    }
+    __syncthreads();
+    if (c0 > R || c0 + CN - 1 < b0) return;   // (no barrier below)
+    typedef double d2 __attribute__((ext_vector_type(2)));
+    const double *pa = B + (int64_t)a * Qp + 2 * kq, *pb = B + (int64_t)b * Qp + 2 * kq, *pw = W + 2 * kq;
+    const double* pc[CN];
+    V4 acc[CN];
+#pragma unroll
+    for (int cn = 0; cn < CN; ++cn) {
+        pc[cn] = B + (int64_t)min(c0 + cn, R) * Qp + 2 * kq;
+        acc[cn] = V4{0.0, 0.0, 0.0, 0.0};
+    }
+    // the next step's loads in flight while this one is contracted
+    d2 va = *(const d2*)pa, vb = *(const d2*)pb, vw = *(const d2*)pw, vc[CN];
+#pragma unroll
+    for (int cn = 0; cn < CN; ++cn) vc[cn] = *(const d2*)pc[cn];
+    for (int q = 0; q < Qp; q += kStep) {
+        const int nq = q + kStep < Qp ? q + kStep : q;
+        const d2 na = *(const d2*)(pa + nq), nb = *(const d2*)(pb + nq), nw = *(const d2*)(pw + nq);
+        d2 nc[CN];
+#pragma unroll
+        for (int cn = 0; cn < CN; ++cn) nc[cn] = *(const d2*)(pc[cn] + nq);
+        const double bx = vb.x * vw.x, by = vb.y * vw.y;
+#pragma unroll
+        for (int cn = 0; cn < CN; ++cn) acc[cn] = __builtin_amdgcn_mfma_f64_16x16x4f64(bx * vc[cn].x, va.x, acc[cn], 0, 0, 0);
+#pragma unroll
+        for (int cn = 0; cn < CN; ++cn) acc[cn] = __builtin_amdgcn_mfma_f64_16x16x4f64(by * vc[cn].y, va.y, acc[cn], 0, 0, 0);
+        va = na;
+        vb = nb;
+        vw = nw;
+#pragma unroll
+        for (int cn = 0; cn < CN; ++cn) vc[cn] = nc[cn];
+    }
+    hankel(b, h);
+#pragma unroll
+    for (int s = 0; s < 3; ++s) {   // the tail: i = 4 s + kq <= kTail (i = kTail + 1 has alpha = 0)
+        const int i = 4 * s + kq;
+        const double ha = sA[wave][row][i];
+#pragma unroll
+        for (int cn = 0; cn < CN; ++cn) {
+            double v = 0.0;
+            for (int j = 0; j <= kTail; ++j) v = fma(h[j], sU[wave][cn][i + j], v);
+            acc[cn] = __builtin_amdgcn_mfma_f64_16x16x4f64(v, ha, acc[cn], 0, 0, 0);
+        }
+    }
+    const int ao = a0 + row;
+#pragma unroll
+    for (int cn = 0; cn < CN; ++cn) {
+        const int c = c0 + cn;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int bo = b0 + kq + 4 * v;   // the f64 result's row
+            if (c <= R && bo <= c && ao <= bo) out[tetra(c) + (int64_t)bo * (bo + 1) / 2 + ao] = acc[cn][v];
+        }
+    }
 }
 
 }  // namespace
@@ -183,10 +366,17 @@ int64_t table_size(int R) { return (int64_t)(R + 1) * (R + 2) * (R + 3) / 6; }
 
 // Host part of the rule for radius R (no heap allocation): T* = 8 R^2 + 64.
 static void make_rule(double s, int R, Rule& rule, TailParams& tp, int& Q) {
+    static const struct Nodes {
+        double x[kGL], w[kGL];
+        Nodes() { gauss_legendre(kGL, x, w); }
+    } gl;
     const double T = 8.0 * R * (double)R + 64.0;
     rule.s = s;
     rule.u_hi = std::log(T);
-    gauss_legendre(kGL, rule.gx, rule.gw);
+    for (int i = 0; i < kGL; ++i) {
+        rule.gx[i] = gl.x[i];
+        rule.gw[i] = gl.w[i];
+    }
     rule.n_lo = 0;
     for (double u = kULo; u < -8.0 - 1e-12; u += 4.0) rule.n_lo++;
     rule.n_hi = 0;
@@ -198,19 +388,31 @@ static void make_rule(double s, int R, Rule& rule, TailParams& tp, int& Q) {
     for (int k = 0; k <= 3 * kTail; ++k) tp.J[k] = c0 * std::ldexp(J[k], -k);
 }
 
-// The three launches on `stream`; scratch: 2 Q + Q (R + 1) doubles (nodes, weights, the
-// scaled Bessel values B[q][n]).
+static int padded_nodes(int Q) { return (Q + kStep - 1) / kStep * kStep; }
+
+// The two launches on `stream`; scratch: Qp (R + 2) doubles, Qp = padded_nodes(Q), 16-byte aligned (weights,
+// then the scaled Bessel values B[n][q]).
 static void launch_table(const Rule& rule, const TailParams& tp, int Q, int R, double* scratch, double* out,
                          hipStream_t stream) {
-    double* dt = scratch;
-    double* dw = scratch + Q;
-    double* dB = scratch + 2 * (int64_t)Q;
-    nodes_kernel<<<(Q + 63) / 64, 64, 0, stream>>>(rule, Q, dt, dw);
+    const int Qp = padded_nodes(Q);
+    double* dw = scratch;
+    double* dB = scratch + Qp;
+    const double hankel_x = (double)R * R + 100.0;
+    // nodes from the panel that holds x = hankel_x on
+    const int panel = std::max(0, std::min(rule.n_hi, (int)((std::log(0.5 * hankel_x) + 8.0) / 1.5)));
+    const int large_q0 = (rule.n_lo + panel) * kGL;
+    const int chain = (Qp + kBesselThreads - 1) / kBesselThreads;
+    const int64_t large = ((int64_t)(Q - large_q0) * (R + 1) + kBesselThreads - 1) / kBesselThreads;
+    bessel_kernel<<<(unsigned)(chain + large), kBesselThreads, 0, stream>>>(rule, Q, Qp, R, chain, large_q0, hankel_x,
+                                                                            dw, dB);
     BAE_HIP_CHECK(hipGetLastError());
-    bessel_kernel<<<(Q + 63) / 64, 64, 0, stream>>>(dt, Q, R, dB);
-    BAE_HIP_CHECK(hipGetLastError());
-    const int64_t E = table_size(R);
-    table_kernel<<<(unsigned)((E + 255) / 256), 256, 0, stream>>>(dB, dw, Q, R, E, tp, out);
+    const int tiles = R / kTile + 1;
+    const unsigned pairs = (unsigned)(tiles * (tiles + 1) / 2);
+    // four values of c share a wavefront's loads of the tile rows (76 us at R = 238; 115 with two); below
+    // R = 128 that leaves too few wavefronts (80 at R = 60, for 1024 SIMDs) and each takes one
+    auto grid = [&](int cn) { return dim3((unsigned)((R + kTableWaves * cn) / (kTableWaves * cn)), pairs); };
+    if (R < 128) table_kernel<1><<<grid(1), kTableWaves * 64, 0, stream>>>(dB, dw, Qp, R, tp, out);
+    else table_kernel<4><<<grid(4), kTableWaves * 64, 0, stream>>>(dB, dw, Qp, R, tp, out);
     BAE_HIP_CHECK(hipGetLastError());
 }
 
@@ -220,7 +422,7 @@ void lgf_table_generate(double s, int R, double* out, hipStream_t stream) {
     int Q = 0;
     make_rule(s, R, rule, tp, Q);
     double* scratch = nullptr;
-    if (hipMalloc((void**)&scratch, sizeof(double) * (2 * (int64_t)Q + (int64_t)Q * (R + 1))) != hipSuccess)
+    if (hipMalloc((void**)&scratch, sizeof(double) * (int64_t)padded_nodes(Q) * (R + 2)) != hipSuccess)
         throw Error{BAE_ERR_OOM, "LGF table scratch allocation failed"};
     try {
         launch_table(rule, tp, Q, R, scratch, out, stream);
@@ -239,7 +441,7 @@ void lgf_table_generate(double s, int R, double* out, hipStream_t stream) {
 // Host code reaches it only through the address hipGetSymbolAddress returns on that
 // device; the array's own name is a host-side stand-in there.
 constexpr int kNoAllocQMax = 540;   // nodes of the rule for any R <= 4096 (at most 520)
-constexpr int64_t kNoAllocDoubles = 2 * (int64_t)kNoAllocQMax + (int64_t)kNoAllocQMax * (kNoAllocMaxR + 1);
+constexpr int64_t kNoAllocDoubles = (int64_t)kNoAllocQMax * (kNoAllocMaxR + 2);
 static __device__ __align__(256) double scratch[kNoAllocDoubles];   // 8.9 MB
 
 static std::mutex g_scratch_mu;
@@ -266,7 +468,7 @@ void lgf_table_generate_noalloc(double s, int R, double* out, hipStream_t stream
     TailParams tp;
     int Q = 0;
     make_rule(s, R, rule, tp, Q);
-    if (Q > kNoAllocQMax) throw Error{BAE_ERR_ARG, "bae_lgf_table_noalloc: quadrature rule exceeds its scratch"};
+    if (padded_nodes(Q) > kNoAllocQMax) throw Error{BAE_ERR_ARG, "bae_lgf_table_noalloc: quadrature rule exceeds its scratch"};
     int device = 0;
     BAE_HIP_CHECK(hipGetDevice(&device));
     launch_table(rule, tp, Q, R, scratch_on(device), out, stream);
