@@ -116,15 +116,14 @@ PEAK_HBM = 8000.0   # GB/s, MI355X HBM3E
 def conv_bytes(z):
     """Algorithmic HBM bytes of one FFT convolution (one right-hand side) on the box of extents
     e with FFT lengths M (bae_sizes conv_box / conv_fft): every pass reads and writes the pruned
-    arrays once -- real box E, half-spectrum rows e0 e1 H2, planes e0 M1 H2, the kernel's
-    transform on one octant H0 H1 H2 (complex 16 B, real 8 B)."""
+    arrays once -- half-spectrum rows e0 e1 H2, planes e0 M1 H2, the kernel's transform on one
+    octant H0 H1 H2 (complex 16 B, real 8 B); the points themselves are small beside them."""
     e, M = z["conv_box"], z["conv_fft"]
     H = [m // 2 + 1 for m in M]
-    E = e[0] * e[1] * e[2]
     rows = e[0] * e[1] * H[2]
     planes = e[0] * M[1] * H[2]
-    return (8 * E + 16 * rows) + (16 * rows + 16 * planes) + (32 * planes + 8 * H[0] * H[1] * H[2]) \
-        + (16 * planes + 16 * rows) + (16 * rows + 8 * E)
+    return 16 * rows + (16 * rows + 16 * planes) + (32 * planes + 8 * H[0] * H[1] * H[2]) \
+        + (16 * planes + 16 * rows) + 16 * rows
 
 
 def fast_summation(torch, P, ctx, step_fft, steps, z, nrhs, q, ref_u, log_name):
@@ -154,7 +153,7 @@ def fast_summation(torch, P, ctx, step_fft, steps, z, nrhs, q, ref_u, log_name):
             "box": zz["conv_box"], "fft_lengths": zz["conv_fft"],
             "roofline": {"bound": "hbm", "achieved": b / t_conv / 1e9, "peak": PEAK_HBM, "unit": "GB/s",
                          "frac": b / t_conv / 1e9 / PEAK_HBM, "bytes_per_convolution": b,
-                         "kernel": "one convolution (HIP events): clear, scatter of the weights, the five FFT passes (conv_z_fwd, conv_lines x3, conv_z_inv), gather; bytes count the FFT passes"}}
+                         "kernel": "one convolution (HIP events): the z spectra of the sources' rows, the y, x and inverse y passes, the z sums at the targets (conv_z_sources, conv_y_fwd, conv_x, conv_y_inv, conv_z_targets)"}}
 
 
 def time_applies(torch, ctx, q, v, prec, reps):

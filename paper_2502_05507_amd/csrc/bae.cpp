@@ -86,19 +86,11 @@ void check_sum_error(bae_ctx* c) {
 // The source weights are FP32 only for the FP32 sum kernels; the FFT convolution takes FP64.
 static int weight_prec(int prec) { return prec == BAE_PREC_FP32 ? BAE_PREC_FP32 : BAE_PREC_FP64; }
 
-// Box indices of a point set's points (internal order) in the convolution box.
-static std::vector<int32_t> conv_indices(const ConvPlan& cp, const PointSet& ps) {
-    std::vector<int32_t> v(ps.count);
-    for (int64_t i = 0; i < ps.count; ++i)
-        v[i] = (int32_t)cp.index(ps.hq[3 * i] / kQuant, ps.hq[3 * i + 1] / kQuant, ps.hq[3 * i + 2] / kQuant);
-    return v;
-}
-
 static void ensure_mplus(bae_ctx* c);
 
 // The FFT convolution of the LGF sum (lazy, once per context): its plan on the box of N+ u E
 // and the box index of every source and target.
-static void ensure_conv(bae_ctx* c, bool mplus = false) {
+static void ensure_conv(bae_ctx* c, int nrhs, bool mplus = false) {
     if (!c->conv) {
         const Geometry& G = c->geo;
         int64_t box = 1;
@@ -106,16 +98,21 @@ static void ensure_conv(bae_ctx* c, bool mplus = false) {
         if (box > INT32_MAX) throw Error{BAE_ERR_ARG, "LGF convolution: box beyond 2^31 nodes"};
         auto cp = std::make_unique<ConvPlan>();
         cp->build(G.bbox_lo, G.bbox_hi, c->tabs, c->stream);
-        upload(c->conv_sidx, conv_indices(*cp, c->S.ps), c->stream);
-        upload(c->conv_tidx, conv_indices(*cp, c->T.ps), c->stream);
-        BAE_HIP_CHECK(hipStreamSynchronize(c->stream));
+        auto src = std::make_unique<ConvPoints>(), tgt = std::make_unique<ConvPoints>();
+        src->build(*cp, c->S.ps, c->stream);
+        tgt->build(*cp, c->T.ps, c->stream);
+        c->conv_src = std::move(src);
+        c->conv_tgt = std::move(tgt);
         c->conv = std::move(cp);
     }
-    if (mplus && !c->conv_midx.p) {
+    if (mplus && !c->conv_mp) {
         ensure_mplus(c);
-        upload(c->conv_midx, conv_indices(*c->conv, c->Mp.ps), c->stream);
-        BAE_HIP_CHECK(hipStreamSynchronize(c->stream));
+        auto mp = std::make_unique<ConvPoints>();
+        mp->build(*c->conv, c->Mp.ps, c->stream);
+        c->conv_mp = std::move(mp);
     }
+    c->conv->reserve(*c->conv_src, *c->conv_tgt, nrhs);
+    if (mplus) c->conv->reserve(*c->conv_mp, *c->conv_mp, nrhs);
 }
 
 // The current operator's LGF sum at the gamma targets (its sources, weights, work list), or
@@ -123,12 +120,9 @@ static void ensure_conv(bae_ctx* c, bool mplus = false) {
 static void apply_lgf(bae_ctx* c, const void* w, int nrhs, int prec, int* chunks_out, hipStream_t st,
                       const int32_t* skip = nullptr) {
     if (prec == BAE_PREC_FFT) {
-        ensure_conv(c);
-        const int32_t* sidx = c->op.direct ? c->conv_tidx.as<int32_t>() : c->conv_sidx.as<int32_t>();
-        const int64_t ldw = c->op.S->padded;
-        for (int r = 0; r < nrhs; ++r)
-            c->conv->apply((const double*)w + r * ldw, sidx, c->op.S->count, c->conv_tidx.as<int32_t>(), c->nT,
-                           c->part.as<double>() + r * c->nT, 1.0, skip, st);
+        ensure_conv(c, nrhs);
+        c->conv->apply((const double*)w, c->op.S->padded, c->op.direct ? *c->conv_tgt : *c->conv_src, *c->conv_tgt,
+                       c->part.as<double>(), c->nT, nrhs, 1.0, skip, st);
         *chunks_out = 1;
         return;
     }
@@ -1041,9 +1035,8 @@ static void rhs_on_device(bae_ctx* c, int nrhs, const double* g, int64_t ldg, bo
     } else if (has_f) {
         // the free-space volume potential h^2 sum_{M+} G(m - n) f(n) on gamma, by the FFT
         // convolution (FP64), in internal target order, then into [gamma+; gamma-] order
-        for (int r = 0; r < nrhs; ++r)
-            c->conv->apply(c->wf.as<double>() + r * nmp, c->conv_midx.as<int32_t>(), c->Mp.ps.count,
-                           c->conv_tidx.as<int32_t>(), c->nT, c->vsum.as<double>() + r * c->nT, 1.0, nullptr, st);
+        c->conv->apply(c->wf.as<double>(), nmp, *c->conv_mp, *c->conv_tgt, c->vsum.as<double>(), c->nT, nrhs, 1.0,
+                       nullptr, st);
         launch_reduce_scatter(c->vsum.as<double>(), 1, c->nT, c->t_pos.as<int32_t>(), c->up_gamma.as<double>(), c->nT,
                               nrhs, 1.0, st);
     } else {
@@ -1083,7 +1076,7 @@ static void set_rhs_impl(bae_ctx* c, int32_t nrhs, const double* g_xstar, const 
             if (!std::isfinite(f_grid[i])) throw Error{BAE_ERR_NONFINITE, "source term not finite"};
         ensure_lin(c);
         if (box) ensure_box(c);
-        else ensure_conv(c, true);
+        else ensure_conv(c, nrhs, true);
         const int64_t nm = c->Mp.ps.count, nmp = c->Mp.ps.padded;
         std::vector<double> wfh(nmp * nrhs, 0.0);
         const double h2 = G.h * G.h;
@@ -1115,7 +1108,7 @@ static void set_rhs_device_impl(bae_ctx* c, int32_t nrhs, const double* g_dev, c
         // caller's work is touched
         ensure_lin(c);
         if (box) ensure_box(c);
-        else ensure_conv(c, true);
+        else ensure_conv(c, nrhs, true);
         const int64_t nmp = c->Mp.ps.padded;
         if (c->wf.bytes < sizeof(double) * nmp * nrhs) c->wf.alloc(sizeof(double) * nmp * c->max_rhs);
         if (box && c->box_u.bytes < sizeof(double) * c->box_nn * nrhs)
@@ -1165,9 +1158,8 @@ static void grid_solution(bae_ctx* c, int nrhs, hipStream_t st) {
         if (c->particular_box)   // the finite-grid u_p is known at every node
             launch_gather(c->box_u.as<double>(), nn, c->box_mpidx.as<int32_t>(), nm, up.as<double>(), nm, nrhs, 1.0, st);
         else   // the free-space volume potential at the M+ targets, by the FFT convolution
-            for (int r = 0; r < nrhs; ++r)
-                c->conv->apply(c->wf.as<double>() + r * c->Mp.ps.padded, c->conv_midx.as<int32_t>(), nm,
-                               c->conv_midx.as<int32_t>(), nm, up.as<double>() + r * nm, 1.0, nullptr, st);
+            c->conv->apply(c->wf.as<double>(), c->Mp.ps.padded, *c->conv_mp, *c->conv_mp, up.as<double>(), nm, nrhs, 1.0,
+                           nullptr, st);
         launch_axpby(1.0, up.as<double>(), nm, 1.0, um.as<double>(), nm, nm, nrhs, st);
         BAE_HIP_CHECK(hipStreamSynchronize(st));   // up leaves scope
     }

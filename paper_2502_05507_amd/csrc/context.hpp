@@ -207,11 +207,11 @@ struct bae_ctx {
     int64_t vec_cap = 0;       // elements per RHS of b, x, r, tmp and the Krylov vectors
     int64_t dens_n = 0;        // length of the last solve's density (|gamma-|, or |gamma| for direct)
     int batch_refs = 0;        // batches holding this context (they keep pointers to its vectors)
-    // the LGF sum by FFT convolution on the box of N+ u E (lazy): the plan, and the box index
-    // of every source (gamma- u E), target (gamma, also the direct formulation's sources) and
-    // M+ point, each in its point set's internal order
+    // the LGF sum by FFT convolution on the box of N+ u E (lazy): the plan, and on its box the
+    // sources (gamma- u E), the targets (gamma, also the direct formulation's sources) and the
+    // M+ points, each in its point set's internal order
     std::unique_ptr<ConvPlan> conv;
-    DevMem conv_sidx, conv_tidx, conv_midx;
+    std::unique_ptr<ConvPoints> conv_src, conv_tgt, conv_mp;
     DevMem cl_tq, cl_tp, cl_t;
     Closure cl;
     std::shared_ptr<Table> table;

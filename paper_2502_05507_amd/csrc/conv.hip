@@ -5,13 +5,19 @@
 // the kernel sampled at the wrapped offsets: g(i) = G(i) for i < e, G(M - i) for i > M - e.
 // G is even in every coordinate, so its transform is real and even: one octant is stored.
 //
-// Per right-hand side the transform is pruned to where data are: the z transforms run on the
-// e0 x e1 rows that hold weights (two real rows per complex FFT) and keep the half spectrum
-// k <= M2/2 of each real row (the rest is its conjugate mirror), the y transforms run on
-// e0 x (M2/2 + 1) lines, the x transforms on all M1 x (M2/2 + 1) lines fused with the product by
-// the kernel's transform and the inverse x transform, which keeps only the e0 planes of the
-// box; the inverse y and z transforms keep only the box again.  All passes are FP64 in LDS.
+// Per right-hand side the transform is pruned to where data are, on half spectra k <= M2/2 along z (real data):
+//   y pass    the z spectra of the e0 x e1 rows, formed from the few points of each row (conv_y_fwd), and the
+//             forward y transforms of e0 x (M2/2 + 1) lines
+//   x pass    forward x transforms of all M1 x (M2/2 + 1) lines, the product by the kernel's transform and the
+//             inverse x transforms, which keep only the e0 planes of the box (conv_x)
+//   y inverse back to the box's rows that hold targets (conv_y_inv)
+//   z         the inverse z transform at the targets of each row, a sum over its half spectrum (conv_z_targets)
+// A set with many points per row (the volume potential's M+) goes through dense rows instead: two real rows per
+// complex z FFT (conv_z_fwd, conv_z_inv).  All passes are FP64; lines transform in LDS.
+#include <algorithm>
 #include <cmath>
+#include <functional>
+#include <mutex>
 
 #include "conv.hpp"
 #include "fft_device.hpp"
@@ -34,7 +40,7 @@ __device__ __forceinline__ int64_t idx3(int i, int j, int k, int n1, int n2) { r
 // F b = (Z_k - conj Z_{-k}) / 2i); the half spectrum k < H2 = M2/2 + 1 into C [e0][M1][H2].
 template <int THREADS>
 __global__ __launch_bounds__(THREADS, 4) void conv_z_fwd(const double* __restrict__ R, int e0, int e1, int e2,
-                                                          int M1, double2* __restrict__ C, const FftDev p, int P,
+                                                          int64_t plane, int K2, double2* __restrict__ C, const FftDev p, int P,
                                                           const int32_t* __restrict__ skip) {
     extern __shared__ double2 lds[];
     __shared__ int64_t cbase[kMaxLinesPerBlock];   // start of row l0 + pl's half spectrum in C (-1: none)
@@ -48,7 +54,7 @@ __global__ __launch_bounds__(THREADS, 4) void conv_z_fwd(const double* __restric
     const int H = M / 2 + 1;
     if ((int)threadIdx.x < P) {
         const int64_t l = l0 + threadIdx.x;
-        cbase[threadIdx.x] = l < nl ? idx3((int)(l / e1), (int)(l % e1), 0, M1, H) : -1;
+        cbase[threadIdx.x] = l < nl ? (l / e1) * plane + (l % e1) * K2 : -1;
     }
     for (int e = threadIdx.x; e < nfft * M; e += blockDim.x) A[e] = make_double2(0.0, 0.0);
     __syncthreads();
@@ -92,95 +98,353 @@ __global__ __launch_bounds__(THREADS, 4) void conv_z_fwd(const double* __restric
     }
 }
 
-// Transforms of complex lines along a strided axis of C: line l, element n at
-// (l / lin) sout + (l % lin) + n sline.  mode 0: forward, elements n < nload loaded (zero
-// beyond), n < nstore stored; mode 1: forward, times the kernel's transform, inverse (the x
-// pass; n < nload loaded and stored); mode 2: inverse, all M loaded, n < nstore stored.
-// P consecutive lines (consecutive in memory) per block.
-// MODE is a template parameter so that each kernel holds only the transforms it runs.
-template <int THREADS, int MODE>
-__global__ __launch_bounds__(THREADS, 4) void conv_lines(double2* __restrict__ C, int64_t nlines, int64_t lin,
-                                                          int64_t sout, int64_t sline, int nload, int nstore,
-                                                          const FftDev p, int P, const double* __restrict__ ghat,
-                                                          int M1, int L2, int H1, int H2,
+// The lines of a block in LDS: buffer, then the root table.
+__device__ __forceinline__ Lines block_lines(double2* lds, int M, int P) {
+    Lines L;
+    L.A = lds;
+    L.P = P;
+    L.M = M;
+    L.LS = M | 1;
+    L.tw = lds + (int64_t)P * L.LS;
+    L.rP = rcp_up(P);
+    return L;
+}
+
+// base[off bytes] with a wavefront-uniform base and a per-lane offset
+template <typename T, typename Off>
+__device__ __forceinline__ T& at_bytes(T* base, Off off) {
+    return *(T*)((char*)base + off);
+}
+
+// a mod M for a < 2^23, M <= kFftMaxLen (magic = floor(2^32 / M) + 1): the quotient by the high product is exact
+// or one too large, and the unsigned minimum takes back the step where it is.
+__device__ __forceinline__ uint32_t mod_by(uint32_t a, uint32_t M, uint32_t magic) {
+    const uint32_t t = a - __umulhi(a, magic) * M;
+    return min(t, t + M);
+}
+
+// Forward transforms along y: the lines k of plane i (element n at n K2 + k) hold the z spectra at k of the plane's
+// rows n of range[i] (all n < e1 without it), zero beyond.  A block takes P lines k of one plane.
+// What bounds it: writing C (318 MB per right-hand side at 257^3): 95 us, 4.8 TB/s (143 us before the register stages).
+template <int THREADS>
+__global__ __launch_bounds__(THREADS, THREADS == kLineThreads ? 3 : 2) void conv_y_fwd(double2* __restrict__ C, int64_t cstride, int kblocks, int e1,
+                                                          int H2, int K2, int64_t plane, const FftDev p, int P, const int2* __restrict__ range,
                                                           const int32_t* __restrict__ skip) {
     extern __shared__ double2 lds[];
-    // per line of the block: its first element in C (-1: past the last line) and, in the x
-    // pass, its row of the kernel's transform; element n is then lbase + n sline
-    __shared__ int64_t lbase[kMaxLinesPerBlock];
-    __shared__ int32_t grow[kMaxLinesPerBlock];
     if (skip && *skip) return;
     const int M = p.M;
-    double2* A = lds;
-    double2* tw = A + (int64_t)P * M;
-    load_roots(p, tw);
+    const Lines L = block_lines(lds, M, P);
+    const int group = xcd_group(blockIdx.x, gridDim.x);
+    const int i = group / kblocks, k0 = (group - i * kblocks) * P;
+    const int2 held = range ? range[i] : make_int2(0, e1 - 1);
+    double2* base = C + (blockIdx.y * cstride + i * plane + k0);
+    const int live = min(P, H2 - k0);
+    load_roots(p, const_cast<double2*>(L.tw));
+    auto st_lds = [&](int pl, int o, int kn, double2 x) { L.A[pl * L.LS + o + kn] = x; };
+    auto ld_lds = [&](int pl, int j, int rm) { return L.A[pl * L.LS + j + rm]; };
+    int Ns = 1;
+    with_radix(p.c[0], [&](auto rc) {
+        constexpr int R = decltype(rc)::value;
+        first_stage<R, THREADS, false, true>(
+            L,
+            [&](int pl, int j, int rm) {
+                const int n = j + rm;
+                return n >= held.x && n <= held.y && pl < live
+                           ? at_bytes(base + (int64_t)rm * K2, 16u * (uint32_t)(j * K2 + pl))
+                           : make_double2(0.0, 0.0);
+            },
+            st_lds);
+        Ns = R;
+    });
+    middle_stages<THREADS, false>(L, p, 1, 1, p.nc - 2, Ns);
+    with_radix(p.c[p.nc - 1], [&](auto rc) {
+        constexpr int R = decltype(rc)::value;
+        last_stage<R, THREADS, false, false>(L, ld_lds, [&](int pl, int o, int kn, double2 x) {
+            if (pl < live) at_bytes(base + (int64_t)kn * K2, 16u * (uint32_t)(o * K2 + pl)) = x;
+        });
+    });
+}
+
+// Inverse transforms along y of the same lines; of each, the rows n of range[i] are kept (all n < e1 without it).
+// What bounds it: reading C: 110 us at 257^3 (139 before the register stages).
+template <int THREADS>
+__global__ __launch_bounds__(THREADS, THREADS == kLineThreads ? 3 : 2) void conv_y_inv(double2* __restrict__ C, int64_t cstride, int kblocks, int e1,
+                                                          int H2, int K2, int64_t plane, const FftDev p, int P, const int2* __restrict__ range,
+                                                          const int32_t* __restrict__ skip) {
+    extern __shared__ double2 lds[];
+    if (skip && *skip) return;
+    const int M = p.M;
+    const Lines L = block_lines(lds, M, P);
+    const int group = xcd_group(blockIdx.x, gridDim.x);
+    const int i = group / kblocks, k0 = (group - i * kblocks) * P;
+    const int2 keep = range ? range[i] : make_int2(0, e1 - 1);
+    if (keep.y < keep.x) return;   // no target in the plane
+    double2* base = C + (blockIdx.y * cstride + i * plane + k0);
+    const int live = min(P, H2 - k0);
+    load_roots(p, const_cast<double2*>(L.tw));
+    auto st_lds = [&](int pl, int o, int kn, double2 x) { L.A[pl * L.LS + o + kn] = x; };
+    auto ld_lds = [&](int pl, int j, int rm) { return L.A[pl * L.LS + j + rm]; };
+    int Ns = 1;
+    with_radix(p.c[0], [&](auto rc) {
+        constexpr int R = decltype(rc)::value;
+        first_stage<R, THREADS, true, false>(
+            L,
+            [&](int pl, int j, int rm) {
+                return pl < live ? at_bytes(base + (int64_t)rm * K2, 16u * (uint32_t)(j * K2 + pl)) : make_double2(0.0, 0.0);
+            },
+            st_lds);
+        Ns = R;
+    });
+    middle_stages<THREADS, true>(L, p, 1, 1, p.nc - 2, Ns);
+    with_radix(p.c[p.nc - 1], [&](auto rc) {
+        constexpr int R = decltype(rc)::value;
+        last_stage<R, THREADS, true, true>(L, ld_lds, [&](int pl, int o, int kn, double2 x) {
+            const int n = o + kn;
+            if (n >= keep.x && n <= keep.y && pl < live) at_bytes(base + (int64_t)kn * K2, 16u * (uint32_t)(o * K2 + pl)) = x;
+        });
+    });
+}
+
+// Forward x transforms (elements n < e0 loaded, zero beyond) of the lines (j, k), P values of k to a block, the
+// product by the kernel's transform (even in every index: one octant), the inverse x transforms (n < e0 stored).
+// The last forward stage leaves in a thread's registers exactly the inputs of the inverse's first stage (the same
+// radix, n = j + k M / R), so the product and the two stages are one step.
+// Off: the type of a lane's byte offset (64 bits where a stage's part of C, or the kernel's transform, passes 4 GB).
+// What bounds it: reading and writing C (e0 of the M0 planes) and reading the kernel's transform, 146 us at 257^3 for
+// memory alone, and about 141 us of vector issue, which three blocks per compute unit overlap little: 287 us per
+// right-hand side (408 with stages of radix at most 5 that passed through LDS six times).  Leaving out the zero half of
+// the first stage and the unwanted half of the last (HALF) costs registers here and made it 295 us.
+template <int THREADS, typename Off>
+__global__ __launch_bounds__(THREADS, THREADS == kLineThreads ? 3 : 2) void conv_x(
+    double2* __restrict__ C, int64_t cstride, int kblocks, int e0, int M1, int H1, int H2, int K2, int64_t plane,
+    const FftDev p, int P, const double* __restrict__ ghat, const int32_t* __restrict__ skip) {
+    extern __shared__ double2 lds[];
+    if (skip && *skip) return;
+    const int M = p.M;
+    const Lines L = block_lines(lds, M, P);
+    const int group = xcd_group(blockIdx.x, gridDim.x);
+    const int row = group / kblocks, k0 = (group - row * kblocks) * P;
+    double2* base = C + (blockIdx.y * cstride + (int64_t)row * K2 + k0);
+    const double* gbase = ghat + ((int64_t)min(row, M1 - row) * K2 + k0);   // its row of the kernel's transform
+    const int live = min(P, H2 - k0);
+    load_roots(p, const_cast<double2*>(L.tw));
+    auto st_lds = [&](int pl, int o, int kn, double2 x) { L.A[pl * L.LS + o + kn] = x; };
+    auto ld_lds = [&](int pl, int j, int rm) { return L.A[pl * L.LS + j + rm]; };
+    int Ns = 1;
+    with_radix(p.c[0], [&](auto rc) {
+        constexpr int R = decltype(rc)::value;
+        first_stage<R, THREADS, false, false>(
+            L,
+            [&](int pl, int j, int rm) {
+                return rm < (pl < live ? e0 - j : 0) ? at_bytes(base + rm * plane, 16 * ((Off)j * (Off)plane + (Off)pl))
+                                                     : make_double2(0.0, 0.0);
+            },
+            st_lds);
+        Ns = R;
+    });
+    middle_stages<THREADS, false>(L, p, 1, 1, p.nc - 2, Ns);
+    with_radix(p.c[p.nc - 1], [&](auto rc) {
+        constexpr int R = decltype(rc)::value;
+        Stage<R, THREADS, false> s;
+        constexpr int I = Stage<R, THREADS, false>::I;
+        const Off gplane = (Off)H1 * (Off)K2;
+        auto kernel_value = [&](int pl, int n) {
+            return at_bytes(gbase, 8 * ((Off)min(n, M - n) * gplane + (Off)pl));
+        };
+        // the values of the kernel's transform are in flight while the forward stage runs, where the registers
+        // (168 of them) hold them beside its points
+        constexpr bool ahead = R <= 16;
+        double g[ahead ? I : 1][R];
+        if constexpr (ahead) {
+#pragma unroll
+            for (int it = 0; it < I; ++it) {
+                const int e = threadIdx.x + it * THREADS;
+                if (e >= P * Ns) continue;
+                const int j = fdiv_up(e, L.rP), pl = e - j * P;
+#pragma unroll
+                for (int k = 0; k < R; ++k) g[it][k] = kernel_value(pl, j + k * Ns);
+            }
+        }
+        s.load(L, Ns, ld_lds);
+        s.transform(L, Ns, 1);
+#pragma unroll
+        for (int it = 0; it < I; ++it) {
+            if (s.o[it] < 0) continue;
+#pragma unroll
+            for (int k = 0; k < R; ++k)
+                s.v[it][k] = cscale(s.v[it][k], ahead ? g[it][k] : kernel_value(s.pl[it], s.o[it] + k * Ns));
+            dft<R, true>(s.v[it]);
+            s.o[it] *= R;   // the inverse's first stage: outputs j R + k
+        }
+        __syncthreads();
+        s.store(1, st_lds);
+        Ns = R;
+    });
+    middle_stages<THREADS, true>(L, p, p.nc - 2, -1, p.nc - 2, Ns);
+    with_radix(p.c[0], [&](auto rc) {
+        constexpr int R = decltype(rc)::value;
+        last_stage<R, THREADS, true, false>(L, ld_lds, [&](int pl, int o, int kn, double2 x) {
+            if (kn < (pl < live ? e0 - o : 0)) at_bytes(base + kn * plane, 16 * ((Off)o * (Off)plane + (Off)pl)) = x;
+        });
+    });
+}
+
+// Complex transforms of all M elements of the lines (l / lin) sout + (l % lin) + n sline of g, in place (the
+// set-up's transforms of the kernel).
+template <int THREADS>
+__global__ __launch_bounds__(THREADS, THREADS == kLineThreads ? 3 : 2) void conv_lines(double2* __restrict__ g, int64_t nlines, int64_t lin,
+                                                          int64_t sout, int64_t sline, const FftDev p, int P) {
+    extern __shared__ double2 lds[];
+    __shared__ int64_t lbase[kMaxLinesPerBlock];
+    const Lines L = block_lines(lds, p.M, P);
     const int64_t l0 = (int64_t)xcd_group(blockIdx.x, gridDim.x) * P;
+    load_roots(p, const_cast<double2*>(L.tw));
     if ((int)threadIdx.x < P) {
         const int64_t l = l0 + threadIdx.x;
         lbase[threadIdx.x] = l < nlines ? (l / lin) * sout + (l % lin) : -1;
-        if constexpr (MODE == 1) {
-            // line l = j L2 + k of the x pass on half spectra (L2 = M2/2 + 1, k <= M2/2); the
-            // transform is even in every index
-            const int j = (int)(l / L2), k = (int)(l % L2);
-            grow[threadIdx.x] = min(j, M1 - j) * H2 + k;
-        }
     }
     __syncthreads();
-    const float rP = rcp_up(P);
-    const int nl = MODE == 2 ? M : nload;
-    // every load of the thread issued before the first LDS write (one memory latency, not eight)
-    {
-        double2 v[kIt];
-#pragma unroll
-        for (int it = 0; it < kIt; ++it) {
-            const int e = threadIdx.x + it * THREADS;
-            v[it] = make_double2(0.0, 0.0);
-            if (e >= P * M) continue;
-            const int n = fdiv_up(e, rP), pl = e - n * P;
-            const int64_t lb = lbase[pl];
-            if (n < nl && lb >= 0) v[it] = C[lb + n * sline];
-        }
-#pragma unroll
-        for (int it = 0; it < kIt; ++it) {
-            const int e = threadIdx.x + it * THREADS;
-            if (e >= P * M) continue;
-            const int n = fdiv_up(e, rP), pl = e - n * P;
-            A[pl * M + n] = v[it];
-        }
-    }
+    auto st_lds = [&](int pl, int o, int kn, double2 x) { L.A[pl * L.LS + o + kn] = x; };
+    auto ld_lds = [&](int pl, int j, int rm) { return L.A[pl * L.LS + j + rm]; };
+    int Ns = 1;
+    with_radix(p.c[0], [&](auto rc) {
+        constexpr int R = decltype(rc)::value;
+        first_stage<R, THREADS, false, false>(L, [&](int pl, int j, int rm) {
+            return lbase[pl] >= 0 ? g[lbase[pl] + (j + rm) * sline] : make_double2(0.0, 0.0);
+        }, st_lds);
+        Ns = R;
+    });
+    middle_stages<THREADS, false>(L, p, 1, 1, p.nc - 2, Ns);
+    with_radix(p.c[p.nc - 1], [&](auto rc) {
+        constexpr int R = decltype(rc)::value;
+        last_stage<R, THREADS, false, false>(L, ld_lds, [&](int pl, int o, int kn, double2 x) {
+            if (lbase[pl] >= 0) g[lbase[pl] + (o + kn) * sline] = x;
+        });
+    });
+}
+
+// The half spectra along z of the rows that hold sources (and of the rows between them): X_k = sum w e^{-2 pi i k z / M2}
+// over the row's sources (z, w).  One wavefront per row, its lanes along k.
+// What bounds it: writing the rows (125 MB per right-hand side at 257^3): 50 us.  Clearing the box, scattering the
+// weights and transforming its dense rows took 95 us.
+constexpr int kZThreads = 256;
+constexpr int kZRows = 4;   // spectral values of a lane in flight
+
+__global__ __launch_bounds__(kZThreads) void conv_z_sources(double2* __restrict__ C, int64_t cstride, int64_t plane, int H2,
+                                                            int K2, const FftDev pz, uint32_t zmagic,
+                                                            const int4* __restrict__ rows, int nrows,
+                                                            const int2* __restrict__ pts, const double* __restrict__ w,
+                                                            int64_t ldw, const int32_t* __restrict__ skip) {
+    extern __shared__ double2 lds[];
+    if (skip && *skip) return;
+    load_roots(pz, lds);
     __syncthreads();
-    double2* Z = A;
-    if constexpr (MODE == 2) fft_lds<THREADS, true>(Z, P, p, tw);
-    else fft_lds<THREADS, false>(Z, P, p, tw);
-    if constexpr (MODE == 1) {   // the product by the kernel's transform, then the inverse
-        const int64_t gplane = (int64_t)H1 * H2;
-        // the block's lines are consecutive rows of the kernel's transform: the line index
-        // fastest, so that a wavefront reads runs of consecutive values of it; all of a
-        // thread's loads issued before the first product (P M <= kIt THREADS)
-        double g[kIt];
+    C += blockIdx.y * cstride;
+    w += blockIdx.y * ldw;
+    const uint32_t M = (uint32_t)pz.M;
+    const int lane = threadIdx.x & 63, waves = gridDim.x * (kZThreads / 64);
+    for (int r = blockIdx.x * (kZThreads / 64) + (threadIdx.x >> 6); r < nrows; r += waves) {
+        const int4 row = rows[r];
+        const int q0 = __builtin_amdgcn_readfirstlane(row.z), q1 = __builtin_amdgcn_readfirstlane(row.w);
+        double2* X = C + (row.x * plane + (int64_t)row.y * K2);
+        for (int k0 = 0; k0 < H2; k0 += 64 * kZRows) {
+            double2 acc[kZRows];
 #pragma unroll
-        for (int it = 0; it < kIt; ++it) {
-            const int e = threadIdx.x + it * THREADS;
-            g[it] = 0.0;
-            if (e >= P * M) continue;
-            const int n = fdiv_up(e, rP), pl = e - n * P;
-            if (lbase[pl] >= 0) g[it] = ghat[min(n, M - n) * gplane + grow[pl]];
-        }
+            for (int u = 0; u < kZRows; ++u) acc[u] = make_double2(0.0, 0.0);
+            for (int q = q0; q < q1; q += 64) {   // (a surface has few sources in a row: one turn)
+                const int nq = min(64, q1 - q);
+                const int2 mine = pts[q + min(lane, nq - 1)];
+                const double wm = w[mine.y];
+                for (int t = 0; t < nq; ++t) {
+                    const uint32_t z = (uint32_t)__builtin_amdgcn_readlane(mine.x, t);
+                    const double x = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(wm), t),
+                                                      __builtin_amdgcn_readlane(__double2loint(wm), t));
+                    const uint32_t step = mod_by(64u * z, M, zmagic);
+                    uint32_t a = mod_by((uint32_t)min(k0 + lane, H2) * z, M, zmagic);
 #pragma unroll
-        for (int it = 0; it < kIt; ++it) {
-            const int e = threadIdx.x + it * THREADS;
-            if (e >= P * M) continue;
-            const int n = fdiv_up(e, rP), pl = e - n * P;
-            const double2 z = Z[(int64_t)pl * M + n];
-            Z[(int64_t)pl * M + n] = make_double2(g[it] * z.x, g[it] * z.y);
+                    for (int u = 0; u < kZRows; ++u) {
+                        const double2 c = lds[a];
+                        acc[u].x = fma(x, c.x, acc[u].x);
+                        acc[u].y = fma(x, c.y, acc[u].y);
+                        a += step;
+                        a = min(a, a - M);
+                    }
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < kZRows; ++u) {
+                const int k = k0 + 64 * u + lane;
+                if (k < H2) X[k] = acc[u];
+            }
         }
-        __syncthreads();
-        fft_lds<THREADS, true>(Z, P, p, tw);
     }
-    for (int e = threadIdx.x; e < P * nstore; e += blockDim.x) {
-        const int n = fdiv_up(e, rP), pl = e - n * P;
-        const int64_t lb = lbase[pl];
-        if (lb >= 0) C[lb + n * sline] = Z[(int64_t)pl * M + n];
+}
+
+// The inverse z transform at the targets of each row (i, j) that holds some: out = scale (X_0 + 2 sum_{0 < k <
+// M2/2} Re X_k e^{2 pi i k z / M2} (+ X_{M2/2} (-1)^z for even M2)).  One wavefront per row, its lanes along k;
+// four targets at a time, whose sums are folded together (each fold halves the lanes and the sums).
+// What bounds it: reading the rows of C that hold targets (125 MB at 257^3): 60 us.  The dense inverse and a gather
+// took 81 us.
+__global__ __launch_bounds__(kZThreads) void conv_z_targets(const double2* __restrict__ C, int64_t cstride, int64_t plane,
+                                                            int H2, int K2, const FftDev pz, uint32_t zmagic,
+                                                            const int4* __restrict__ rows, int nrows,
+                                                            const int2* __restrict__ pts, double* __restrict__ out,
+                                                            int64_t ldo, double scale, const int32_t* __restrict__ skip) {
+    extern __shared__ double2 lds[];
+    if (skip && *skip) return;
+    load_roots(pz, lds);
+    __syncthreads();
+    C += blockIdx.y * cstride;
+    out += blockIdx.y * ldo;
+    const uint32_t M = (uint32_t)pz.M;
+    const int lane = threadIdx.x & 63, waves = gridDim.x * (kZThreads / 64);
+    for (int r = blockIdx.x * (kZThreads / 64) + (threadIdx.x >> 6); r < nrows; r += waves) {
+        const int4 row = rows[r];
+        const int q0 = __builtin_amdgcn_readfirstlane(row.z), q1 = __builtin_amdgcn_readfirstlane(row.w);
+        const double2* X = C + (row.x * plane + (int64_t)row.y * K2);
+        for (int q = q0; q < q1; q += 64) {   // (a surface has few targets in a row: one turn)
+            const int nq = min(64, q1 - q);
+            const int2 mine = pts[q + min(lane, nq - 1)];
+            double sum = 0.0;   // of target q + lane
+            for (int k0 = 0; k0 < H2; k0 += 64 * kZRows) {
+                double2 x[kZRows];
+#pragma unroll
+                for (int u = 0; u < kZRows; ++u) {
+                    const int k = k0 + 64 * u + lane;
+                    x[u] = k < H2 ? X[k] : make_double2(0.0, 0.0);
+                    if (k > 0 && 2 * k < (int)M) x[u] = cscale(x[u], 2.0);
+                }
+                for (int t0 = 0; t0 < nq; t0 += 4) {
+                    double v[4];
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) {
+                        const uint32_t z = (uint32_t)__builtin_amdgcn_readlane(mine.x, min(t0 + t, nq - 1));
+                        const uint32_t step = mod_by(64u * z, M, zmagic);
+                        uint32_t a = mod_by((uint32_t)min(k0 + lane, H2) * z, M, zmagic);
+                        double s = 0.0;
+#pragma unroll
+                        for (int u = 0; u < kZRows; ++u) {
+                            const double2 c = lds[a];   // (cos, -sin)
+                            s = fma(x[u].x, c.x, s);
+                            s = fma(x[u].y, c.y, s);
+                            a += step;
+                            a = min(a, a - M);
+                        }
+                        v[t] = s;
+                    }
+                    // lanes 16 t .. 16 t + 15 end with the sum of target t0 + t
+                    const bool up = lane & 32, odd = lane & 16;
+                    const double p0 = (up ? v[2] : v[0]) + __shfl_xor(up ? v[0] : v[2], 32, 64);
+                    const double p1 = (up ? v[3] : v[1]) + __shfl_xor(up ? v[1] : v[3], 32, 64);
+                    double s = (odd ? p1 : p0) + __shfl_xor(odd ? p0 : p1, 16, 64);
+#pragma unroll
+                    for (int o = 8; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+                    const double got = __shfl(s, ((lane - t0) & 3) * 16, 64);
+                    if ((unsigned)(lane - t0) < 4u) sum += got;
+                }
+            }
+            if (lane < nq) out[mine.y] = scale * sum;
+        }
     }
 }
 
@@ -189,7 +453,7 @@ __global__ __launch_bounds__(THREADS, 4) void conv_lines(double2* __restrict__ C
 // F^-1(X_a + i X_b) = a + i b), n < e2 kept, times scale, into R.
 template <int THREADS>
 __global__ __launch_bounds__(THREADS, 4) void conv_z_inv(const double2* __restrict__ C, int e0, int e1, int e2,
-                                                          int M1, double* __restrict__ R, const FftDev p, int P,
+                                                          int64_t plane, int K2, double* __restrict__ R, const FftDev p, int P,
                                                           double scale, const int32_t* __restrict__ skip) {
     extern __shared__ double2 lds[];
     __shared__ int64_t cbase[kMaxLinesPerBlock];   // start of row l0 + pl's half spectrum in C (-1: none)
@@ -202,7 +466,7 @@ __global__ __launch_bounds__(THREADS, 4) void conv_z_inv(const double2* __restri
     const int H = M / 2 + 1;
     if ((int)threadIdx.x < P) {
         const int64_t l = l0 + threadIdx.x;
-        cbase[threadIdx.x] = l < nl ? idx3((int)(l / e1), (int)(l % e1), 0, M1, H) : -1;
+        cbase[threadIdx.x] = l < nl ? (l / e1) * plane + (l % e1) * K2 : -1;
     }
     __syncthreads();
     const float rM = rcp_up(M), re2 = rcp_up(e2);
@@ -268,13 +532,13 @@ __global__ void conv_kernel_grid(double2* __restrict__ g, int M0, int M1, int M2
     g[q] = make_double2(v, 0.0);
 }
 
-// The real part of the transformed kernel on the octant [H0][H1][H2].
-__global__ void conv_octant(const double2* __restrict__ g, int M1, int M2, int H0, int H1, int H2,
+// The real part of the transformed kernel on the octant [H0][H1][H2] (rows K2 apart).
+__global__ void conv_octant(const double2* __restrict__ g, int M1, int M2, int H0, int H1, int H2, int K2,
                             double* __restrict__ out) {
     const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= (int64_t)H0 * H1 * H2) return;
-    const int a = (int)(q / ((int64_t)H1 * H2)), b = (int)((q / H2) % H1), c = (int)(q % H2);
-    out[q] = g[idx3(a, b, c, M1, M2)].x;
+    if (q >= (int64_t)H0 * H1 * K2) return;
+    const int a = (int)(q / ((int64_t)H1 * K2)), b = (int)((q / K2) % H1), c = (int)(q % K2);
+    out[q] = c < H2 ? g[idx3(a, b, c, M1, M2)].x : 0.0;
 }
 
 __global__ void conv_scatter(const double* __restrict__ w, const int32_t* __restrict__ sidx, int64_t ns,
@@ -295,80 +559,99 @@ __global__ void conv_fill(double* __restrict__ x, int64_t n, const int32_t* __re
     if (i < n) x[i] = 0.0;
 }
 
-// Lines per block of a pass (fft_lines_per_block); packed real rows go two to a complex line.
-int lines_for(int M, bool packed) {
-    const int P = packed ? 2 * fft_lines_per_block(M, 16) : fft_lines_per_block(M, 32);
+// Lines per block of the dense z passes: two packed real rows to a complex line.
+int rows_for(int M) {
+    const int P = 2 * fft_lines_per_block(M, 16);
     if (P > kMaxLinesPerBlock) throw Error{BAE_ERR_ARG, "LGF convolution: too many lines per block"};
     return P;
 }
 
 // The passes run 256-thread blocks of a quarter of the points and LDS, four to a compute unit,
 // so that some blocks' loads and stores overlap the others' LDS stages (a 1024-thread block at
-// 128 VGPRs holds a compute unit alone and runs its phases in series: two blocks of 512 took
-// the 257^3 convolution from 1.41 to 1.21 ms, four of 256 to 1.18 ms, eight of 128 took 1.35 ms);
-// lines longer than such a block holds (2048)
-// keep the 1024-thread blocks.
+// 128 VGPRs holds a compute unit alone and runs its phases in series);
+// lines longer than such a block holds (2048) take 1024-thread blocks.
 constexpr int kSplit = 4;
 constexpr int kSplitThreads = kConvThreads / kSplit;
 constexpr size_t kSplitLdsBytes = kFftLdsBytes / kSplit;
 bool split_blocks(int M) { return M <= kFftPointsPerThread * kSplitThreads; }   // one line fits a block
-int split_lines(int M, bool packed = false) {
+int split_rows(int M) {
     const int by_points = kFftPointsPerThread * kSplitThreads / M;
     const int by_lds = (int)(kSplitLdsBytes / (16 * (size_t)M)) - 1;
-    const int c = std::max(1, std::min(packed ? kMaxLinesPerBlock / 2 : kMaxLinesPerBlock, std::min(by_points, by_lds)));
-    return packed ? 2 * c : c;
+    return 2 * std::max(1, std::min(kMaxLinesPerBlock / 2, std::min(by_points, by_lds)));
 }
+// The register-stage passes: kLineBlocks blocks to a compute unit, of four wavefronts at up to 168 VGPRs.
+constexpr int kLineBlocks = 3;
+bool short_lines(int M) { return M <= 8 * kLineThreads; }
+// Lines per block (the LDS holds their root table beside them): those for which the wavefronts' turns through the
+// stages, at about 9 + 14 R instructions each, are fewest per line.  A wavefront pays for a whole turn however
+// few of its lanes hold a butterfly: at M = 375 = 25 15, eight lines are 120 and 200 butterflies (2 and 4 wavefronts).
+int lines_for(const FftDev& p) {
+    const int threads = short_lines(p.M) ? kLineThreads : kLongThreads;
+    const size_t budget = short_lines(p.M) ? kFftLdsBytes / kLineBlocks : kFftLdsBytes;
+    const int most = std::min(kMaxLinesPerBlock, (int)((budget / sizeof(double2) - p.M) / (p.M | 1)));
+    int best = 1;
+    double best_cost = 1e300;
+    for (int P = 1; P <= most; ++P) {
+        double cost = 0.0;
+        for (int s = 0; s < p.nc; ++s) {
+            const int waves = (P * (p.M / p.c[s]) + 63) / 64;
+            if (P * (p.M / p.c[s]) > threads * fft_items(p.c[s], threads)) cost = 1e300;
+            cost += (double)waves * (9.0 + 14.0 * p.c[s]);
+        }
+        if (cost / P <= best_cost) {
+            best_cost = cost / P;
+            best = P;
+        }
+    }
+    return best;
+}
+size_t lines_lds(int M, int P, int roots) { return sizeof(double2) * ((size_t)P * (M | 1) + roots); }
+
+uint32_t mod_magic(int M) { return (uint32_t)((1ull << 32) / (uint64_t)M) + 1u; }
 
 void set_lds_attr() {
-    static bool done = false;
-    if (done) return;
-    for (const void* f : {(const void*)conv_z_fwd<kConvThreads>, (const void*)conv_z_fwd<kSplitThreads>,
-                          (const void*)conv_lines<kConvThreads, 0>, (const void*)conv_lines<kSplitThreads, 0>,
-                          (const void*)conv_lines<kConvThreads, 1>, (const void*)conv_lines<kSplitThreads, 1>,
-                          (const void*)conv_lines<kConvThreads, 2>, (const void*)conv_lines<kSplitThreads, 2>,
-                          (const void*)conv_z_inv<kConvThreads>, (const void*)conv_z_inv<kSplitThreads>})
-        BAE_HIP_CHECK(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kFftLdsBytes));
-    done = true;
+    static std::once_flag once;   // (per process: the attribute holds for every device of one architecture)
+    std::call_once(once, [] {
+        for (const void* f :
+             {(const void*)conv_z_fwd<kConvThreads>, (const void*)conv_z_fwd<kSplitThreads>,
+              (const void*)conv_z_inv<kConvThreads>, (const void*)conv_z_inv<kSplitThreads>,
+              (const void*)conv_y_fwd<kLongThreads>, (const void*)conv_y_fwd<kLineThreads>,
+              (const void*)conv_y_inv<kLongThreads>, (const void*)conv_y_inv<kLineThreads>,
+              (const void*)conv_x<kLongThreads, uint64_t>, (const void*)conv_x<kLineThreads, uint64_t>,
+              (const void*)conv_x<kLongThreads, uint32_t>, (const void*)conv_x<kLineThreads, uint32_t>,
+              (const void*)conv_lines<kLongThreads>, (const void*)conv_lines<kLineThreads>,
+              (const void*)conv_z_sources, (const void*)conv_z_targets})
+            BAE_HIP_CHECK(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kFftLdsBytes));
+    });
 }
 
-// conv_lines for a mode known at run time
-template <int THREADS, typename... A>
-void launch_lines(int mode, unsigned grid, size_t lds, hipStream_t st, A... args) {
-    if (mode == 0) conv_lines<THREADS, 0><<<grid, THREADS, lds, st>>>(args...);
-    else if (mode == 1) conv_lines<THREADS, 1><<<grid, THREADS, lds, st>>>(args...);
-    else if (mode == 2) conv_lines<THREADS, 2><<<grid, THREADS, lds, st>>>(args...);
-    else throw Error{BAE_ERR_ARG, "LGF convolution: unknown line-pass mode"};
-}
+// Blocks of P lines each
+unsigned groups_of(int64_t nlines, int P) { return (unsigned)((nlines + P - 1) / P); }
 
-// C lines along y (i < e0, k < M2; j the element) or x (j < M1, k < M2; i the element)
-void run_lines(const ConvPlan& cp, double2* C, int axis, int nload, int nstore, int mode, const int32_t* skip,
-               hipStream_t st) {
-    const int M1 = cp.M[1], M2 = cp.M[2];
-    const FftDev& p = axis == 1 ? cp.fy : cp.fx;
-    int64_t nlines, lin, sout, sline;
-    const int H2 = cp.H[2];   // the half spectrum along z
-    if (axis == 1) {
-        nlines = (int64_t)cp.e[0] * H2;
-        lin = H2;
-        sout = (int64_t)M1 * H2;
-        sline = H2;
-    } else {
-        nlines = (int64_t)M1 * H2;
-        lin = nlines;
-        sout = 0;
-        sline = (int64_t)M1 * H2;
-    }
-    const bool split = split_blocks(p.M);
-    const int P = split ? split_lines(p.M) : lines_for(p.M, false);
-    const size_t lds = sizeof(double2) * ((size_t)P + 1) * p.M;
-    const unsigned grid = (unsigned)((nlines + P - 1) / P);
-    if (split)
-        launch_lines<kSplitThreads>(mode, grid, lds, st, C, nlines, lin, sout, sline, nload, nstore, p, P, cp.ghat, M1,
-                                    H2, cp.H[1], cp.H[2], skip);
+// A transform pass of the set-up over every line of the kernel's grid.
+void kernel_pass(double2* g, int64_t nlines, int64_t lin, int64_t sout, int64_t sline, const FftDev& p, hipStream_t st) {
+    const int P = lines_for(p);
+    const size_t lds = lines_lds(p.M, P, p.M);
+    if (short_lines(p.M))
+        conv_lines<kLineThreads><<<groups_of(nlines, P), kLineThreads, lds, st>>>(g, nlines, lin, sout, sline, p, P);
     else
-        launch_lines<kConvThreads>(mode, grid, lds, st, C, nlines, lin, sout, sline, nload, nstore, p, P, cp.ghat, M1,
-                                   H2, cp.H[1], cp.H[2], skip);
+        conv_lines<kLongThreads><<<groups_of(nlines, P), kLongThreads, lds, st>>>(g, nlines, lin, sout, sline, p, P);
     BAE_HIP_CHECK(hipGetLastError());
+}
+
+// A set's z transforms as sums over its points: a spectral value costs an LDS read and two fused multiply-adds per
+// point of its row there, and a whole set of LDS stages by FFT.  Surfaces have 5 to 6 points per row, a volume's
+// rows tens.
+constexpr int64_t kSparseRow = 16;
+
+// Right-hand sides whose grids C stay in the 256 MB memory-side cache together (at least one).
+constexpr int64_t kCacheBytes = 128ll << 20;
+
+void device_alloc(void** p, size_t n) {
+    if (hipMalloc(p, n) != hipSuccess) {
+        *p = nullptr;
+        throw Error{BAE_ERR_OOM, "LGF convolution: device allocation failed"};
+    }
 }
 
 }  // namespace
@@ -380,6 +663,61 @@ int fft_smooth_length(int n) {
             while (r % q == 0) r /= q;
         if (r == 1) return m;
     }
+}
+
+ConvPoints::~ConvPoints() { (void)hipFree(mem); }
+
+void ConvPoints::build(const ConvPlan& cp, const PointSet& ps, hipStream_t st) {
+    const int e0 = cp.e[0], e1 = cp.e[1], e2 = cp.e[2];
+    const int64_t nr = (int64_t)e0 * e1;
+    n = ps.count;
+    sparse = n > 0 && n <= kSparseRow * nr;
+    auto coord = [&](int64_t i, int a) { return ps.hq[3 * i + a] / kQuant - cp.lo[a]; };
+    std::vector<int32_t> row_of(n);
+    for (int64_t i = 0; i < n; ++i) row_of[i] = coord(i, 0) * e1 + coord(i, 1);
+    if (!sparse) {
+        std::vector<int32_t> at_host(n);
+        for (int64_t i = 0; i < n; ++i) at_host[i] = row_of[i] * e2 + coord(i, 2);
+        device_alloc(&mem, sizeof(int32_t) * std::max<int64_t>(n, 1));
+        at = (int32_t*)mem;
+        if (n > 0) BAE_HIP_CHECK(hipMemcpyAsync(mem, at_host.data(), sizeof(int32_t) * n, hipMemcpyHostToDevice, st));
+        BAE_HIP_CHECK(hipStreamSynchronize(st));
+        return;
+    }
+    std::vector<int32_t> ptr(nr + 1, 0);
+    std::vector<int2> range_host(e0, make_int2(e1, -1));
+    for (int32_t r : row_of) ptr[r + 1]++;
+    nrows = 0;
+    for (int i = 0; i < e0; ++i) {
+        int2& g = range_host[i];
+        for (int j = 0; j < e1; ++j) {
+            int32_t* p = &ptr[(int64_t)i * e1 + j];
+            if (p[1]) {
+                g.x = std::min(g.x, j);
+                g.y = j;
+            }
+            p[1] += p[0];
+        }
+        if (g.y >= g.x) nrows += g.y - g.x + 1;
+    }
+    // one allocation and one copy: rows, points, ranges
+    const size_t rows_bytes = sizeof(int4) * nrows, pts_bytes = sizeof(int2) * n, range_bytes = sizeof(int2) * e0;
+    std::vector<char> host(rows_bytes + pts_bytes + range_bytes);
+    int4* rows_host = (int4*)host.data();
+    int2* pts_host = (int2*)(host.data() + rows_bytes);
+    for (int i = 0; i < e0; ++i)
+        for (int j = range_host[i].x; j <= range_host[i].y; ++j) {
+            const int64_t r = (int64_t)i * e1 + j;
+            *rows_host++ = make_int4(i, j, ptr[r], ptr[r + 1]);
+        }
+    for (int64_t i = 0; i < n; ++i) pts_host[ptr[row_of[i]]++] = make_int2(coord(i, 2), (int)i);
+    std::copy(range_host.begin(), range_host.end(), (int2*)(host.data() + rows_bytes + pts_bytes));
+    device_alloc(&mem, host.size());
+    rows = (int4*)mem;
+    pts = (int2*)((char*)mem + rows_bytes);
+    range = (int2*)((char*)mem + rows_bytes + pts_bytes);
+    BAE_HIP_CHECK(hipMemcpyAsync(mem, host.data(), host.size(), hipMemcpyHostToDevice, st));
+    BAE_HIP_CHECK(hipStreamSynchronize(st));   // the host vectors are released here
 }
 
 ConvPlan::~ConvPlan() {
@@ -396,74 +734,147 @@ void ConvPlan::build(const int lo_[3], const int hi_[3], const SumTables& tabs, 
         if (M[a] > kFftMaxLen) throw Error{BAE_ERR_ARG, "LGF convolution: box too long for the LDS FFT"};
         H[a] = M[a] / 2 + 1;
     }
+    K2 = (H[2] + 7) / 8 * 8;
     set_lds_attr();
     fx = fft_plan(M[0], st);
+    // the x pass holds the kernel's transform beside the points of its last radix: the smallest
+    std::sort(fx.c, fx.c + fx.nc, std::greater<int>());
     fy = fft_plan(M[1], st);
     fz = fft_plan(M[2], st);
-    const int64_t full = (int64_t)M[0] * M[1] * M[2], oct = (int64_t)H[0] * H[1] * H[2];
-    const int64_t box = (int64_t)e[0] * e[1] * e[2], cbytes = (int64_t)e[0] * M[1] * H[2];
-    auto dmalloc = [](void** p, size_t n) {
-        if (hipMalloc(p, n) != hipSuccess) throw Error{BAE_ERR_OOM, "LGF convolution: device allocation failed"};
-    };
-    dmalloc((void**)&ghat, sizeof(double) * oct);
-    dmalloc((void**)&R, sizeof(double) * box);
-    dmalloc((void**)&C, sizeof(double2) * cbytes);
-    bytes = sizeof(double) * (oct + box) + sizeof(double2) * cbytes;
+    if (!fx.nc || !fy.nc || !fz.nc) throw Error{BAE_ERR_ARG, "LGF convolution: a length without register radices"};
+    const int64_t full = (int64_t)M[0] * M[1] * M[2], oct = (int64_t)H[0] * H[1] * K2;
+    plane = (int64_t)M[1] * K2;
+    const int64_t one = (int64_t)sizeof(double2) * e[0] * plane;
+    device_alloc((void**)&ghat, sizeof(double) * oct);
+    device_alloc((void**)&C, one);
+    nc = 1;
+    bytes = sizeof(double) * oct + one;
     // the kernel's transform: sample, three full passes (z, y, x), keep one octant
     double2* g = nullptr;
-    dmalloc((void**)&g, sizeof(double2) * full);
-    conv_kernel_grid<<<(unsigned)((full + 255) / 256), 256, 0, st>>>(g, M[0], M[1], M[2], e[0], e[1], e[2],
-                                                                      tabs.full64, tabs.tab_r64, tabs.full_r,
-                                                                      tabs.far64() ? 1 : 0);
-    BAE_HIP_CHECK(hipGetLastError());
-    {   // z: rows of the full grid (complex, contiguous)
-        const int P = lines_for(M[2], false);
-        const int64_t nl = (int64_t)M[0] * M[1];
-        conv_lines<kConvThreads, 0><<<(unsigned)((nl + P - 1) / P), kConvThreads, sizeof(double2) * ((size_t)P + 1) * M[2], st>>>(
-            g, nl, 1, M[2], 1, M[2], M[2], fz, P, nullptr, M[1], M[2], H[1], H[2], nullptr);
+    device_alloc((void**)&g, sizeof(double2) * full);
+    try {
+        conv_kernel_grid<<<(unsigned)((full + 255) / 256), 256, 0, st>>>(g, M[0], M[1], M[2], e[0], e[1], e[2],
+                                                                          tabs.full64, tabs.tab_r64, tabs.full_r,
+                                                                          tabs.far64() ? 1 : 0);
         BAE_HIP_CHECK(hipGetLastError());
+        kernel_pass(g, (int64_t)M[0] * M[1], 1, M[2], 1, fz, st);                              // rows
+        kernel_pass(g, (int64_t)M[0] * M[2], M[2], (int64_t)M[1] * M[2], M[2], fy, st);        // columns of every plane
+        kernel_pass(g, (int64_t)M[1] * M[2], (int64_t)M[1] * M[2], 0, (int64_t)M[1] * M[2], fx, st);
+        conv_octant<<<(unsigned)((oct + 255) / 256), 256, 0, st>>>(g, M[1], M[2], H[0], H[1], H[2], K2, ghat);
+        BAE_HIP_CHECK(hipGetLastError());
+        BAE_HIP_CHECK(hipStreamSynchronize(st));
+    } catch (...) {
+        (void)hipStreamSynchronize(st);
+        (void)hipFree(g);
+        throw;
     }
-    {   // y over every plane, x over every line
-        const int P = lines_for(M[1], false);
-        const int64_t nl = (int64_t)M[0] * M[2];
-        conv_lines<kConvThreads, 0><<<(unsigned)((nl + P - 1) / P), kConvThreads, sizeof(double2) * ((size_t)P + 1) * M[1], st>>>(
-            g, nl, M[2], (int64_t)M[1] * M[2], M[2], M[1], M[1], fy, P, nullptr, M[1], M[2], H[1], H[2], nullptr);
-        BAE_HIP_CHECK(hipGetLastError());
-        const int Px = lines_for(M[0], false);
-        const int64_t nlx = (int64_t)M[1] * M[2];
-        conv_lines<kConvThreads, 0><<<(unsigned)((nlx + Px - 1) / Px), kConvThreads, sizeof(double2) * ((size_t)Px + 1) * M[0], st>>>(
-            g, nlx, nlx, 0, nlx, M[0], M[0], fx, Px, nullptr, M[1], M[2], H[1], H[2], nullptr);
-        BAE_HIP_CHECK(hipGetLastError());
-    }
-    conv_octant<<<(unsigned)((oct + 255) / 256), 256, 0, st>>>(g, M[1], M[2], H[0], H[1], H[2], ghat);
-    BAE_HIP_CHECK(hipGetLastError());
-    BAE_HIP_CHECK(hipStreamSynchronize(st));
     (void)hipFree(g);
 }
 
-void ConvPlan::apply(const double* w, const int32_t* sidx, int64_t ns, const int32_t* tidx, int64_t nt, double* out,
-                     double scale, const int32_t* skip, hipStream_t st) {
-    const int64_t box = (int64_t)e[0] * e[1] * e[2];
-    conv_fill<<<(unsigned)((box + 255) / 256), 256, 0, st>>>(R, box, skip);
-    if (ns > 0) conv_scatter<<<(unsigned)((ns + 255) / 256), 256, 0, st>>>(w, sidx, ns, R);
-    BAE_HIP_CHECK(hipGetLastError());
-    const bool splitz = split_blocks(M[2]);
-    const int Pz = splitz ? split_lines(M[2], true) : lines_for(M[2], true);
+void ConvPlan::reserve(const ConvPoints& src, const ConvPoints& tgt, int nrhs) {
+    const int64_t one = (int64_t)sizeof(double2) * e[0] * plane;
+    const int want = (int)std::max<int64_t>(1, std::min<int64_t>(nrhs, kCacheBytes / one));
+    if (want > nc) {   // (the free waits for whatever still uses the smaller one)
+        BAE_HIP_CHECK(hipFree(C));
+        C = nullptr;
+        bytes -= one * nc;
+        nc = 0;
+        device_alloc((void**)&C, one * want);
+        nc = want;
+        bytes += one * nc;
+    }
+    if (!R && !(src.sparse && tgt.sparse)) {
+        const int64_t box = (int64_t)e[0] * e[1] * e[2];
+        device_alloc((void**)&R, sizeof(double) * box);
+        bytes += sizeof(double) * box;
+    }
+}
+
+void ConvPlan::apply(const double* w, int64_t ldw, const ConvPoints& src, const ConvPoints& tgt, double* out, int64_t ldo,
+                     int nrhs, double scale, const int32_t* skip, hipStream_t st) {
+    reserve(src, tgt, nrhs);
+    const int64_t box = (int64_t)e[0] * e[1] * e[2], one = (int64_t)e[0] * plane;
     const int64_t nrow = (int64_t)e[0] * e[1];
-    const size_t ldsz = sizeof(double2) * (size_t)(Pz / 2 + 1) * M[2];   // Pz / 2 complex lines, the roots
-    const unsigned gz = (unsigned)((nrow + Pz - 1) / Pz);
-    if (splitz) conv_z_fwd<kSplitThreads><<<gz, kSplitThreads, ldsz, st>>>(R, e[0], e[1], e[2], M[1], C, fz, Pz, skip);
-    else conv_z_fwd<kConvThreads><<<gz, kConvThreads, ldsz, st>>>(R, e[0], e[1], e[2], M[1], C, fz, Pz, skip);
-    BAE_HIP_CHECK(hipGetLastError());
-    run_lines(*this, C, 1, e[1], M[1], 0, skip, st);   // y forward: rows j < e1 hold data
-    run_lines(*this, C, 0, e[0], e[0], 1, skip, st);   // x forward, product, x inverse
-    run_lines(*this, C, 1, M[1], e[1], 2, skip, st);   // y inverse: keep j < e1
     const double norm = scale / ((double)M[0] * M[1] * M[2]);
-    if (splitz) conv_z_inv<kSplitThreads><<<gz, kSplitThreads, ldsz, st>>>(C, e[0], e[1], e[2], M[1], R, fz, Pz, norm, skip);
-    else conv_z_inv<kConvThreads><<<gz, kConvThreads, ldsz, st>>>(C, e[0], e[1], e[2], M[1], R, fz, Pz, norm, skip);
-    BAE_HIP_CHECK(hipGetLastError());
-    if (nt > 0) conv_gather<<<(unsigned)((nt + 255) / 256), 256, 0, st>>>(R, tidx, nt, out);
-    BAE_HIP_CHECK(hipGetLastError());
+    const uint32_t zmagic = mod_magic(M[2]);
+    const bool splitz = split_blocks(M[2]);
+    const int Pz = splitz ? split_rows(M[2]) : rows_for(M[2]);
+    const size_t ldsz = sizeof(double2) * (size_t)(Pz / 2 + 1) * M[2];   // Pz / 2 complex lines, the roots
+    const unsigned gz = groups_of(nrow, Pz);
+    // with(block size of a line pass)
+    auto lines = [&](int len, auto&& with) {
+        if (short_lines(len)) with(std::integral_constant<int, kLineThreads>{});
+        else with(std::integral_constant<int, kLongThreads>{});
+        BAE_HIP_CHECK(hipGetLastError());
+    };
+    auto rows = [&](auto&& with) {
+        if (splitz) with(std::integral_constant<int, kSplitThreads>{});
+        else with(std::integral_constant<int, kConvThreads>{});
+        BAE_HIP_CHECK(hipGetLastError());
+    };
+    for (int r0 = 0; r0 < nrhs; r0 += nc) {
+        const int nr = std::min(nc, nrhs - r0);
+        const double* wr = w + r0 * ldw;
+        double* outr = out + r0 * ldo;
+        // eight blocks per compute unit, each of whose wavefronts walks rows (one row to a wavefront, with 1024-thread
+        // blocks, took 72 and 87 us for the two z kernels at 257^3, against 50 and 62)
+        auto zgrid = [&](const ConvPoints& p) { return dim3(std::min(groups_of(p.nrows, kZThreads / 64), 8u * 256u), nr); };
+        if (src.sparse) {
+            conv_z_sources<<<zgrid(src), kZThreads, sizeof(double2) * M[2], st>>>(
+                C, one, plane, H[2], K2, fz, zmagic, src.rows, (int)src.nrows, src.pts, wr, ldw, skip);
+            BAE_HIP_CHECK(hipGetLastError());
+        } else {
+            for (int r = 0; r < nr; ++r) {
+                conv_fill<<<(unsigned)((box + 255) / 256), 256, 0, st>>>(R, box, skip);
+                if (src.n > 0) conv_scatter<<<(unsigned)((src.n + 255) / 256), 256, 0, st>>>(wr + r * ldw, src.at, src.n, R);
+                rows([&](auto t) {
+                    conv_z_fwd<decltype(t)::value><<<gz, decltype(t)::value, ldsz, st>>>(R, e[0], e[1], e[2], plane, K2,
+                                                                                         C + r * one, fz, Pz, skip);
+                });
+            }
+        }
+        // the blocks of a pass take lines of one plane (y) or row (x): kblocks blocks of P lines for each
+        const int P = lines_for(fy), kblocks = (H[2] + P - 1) / P;
+        const dim3 ygrid((unsigned)(e[0] * kblocks), nr);
+        const size_t ylds = lines_lds(M[1], P, M[1]);
+        lines(M[1], [&](auto t) {
+            constexpr int T = decltype(t)::value;
+            conv_y_fwd<T><<<ygrid, T, ylds, st>>>(C, one, kblocks, e[1], H[2], K2, plane, fy, P, src.sparse ? src.range : nullptr, skip);
+        });
+        const int Px = lines_for(fx), xblocks = (H[2] + Px - 1) / Px;
+        lines(M[0], [&](auto t) {
+            constexpr int T = decltype(t)::value;
+            const dim3 grid((unsigned)(M[1] * xblocks), nr);
+            const size_t bytes_lds = lines_lds(M[0], Px, M[0]);
+            // a lane's offset: within the largest M / R planes of C, or the kernel's transform
+            const int rmin = *std::min_element(fx.c, fx.c + fx.nc);
+            const int64_t reach = std::max((int64_t)(M[0] / rmin + 1) * plane * (int64_t)sizeof(double2),
+                                           (int64_t)sizeof(double) * H[0] * H[1] * K2);
+            if (reach < (1ll << 32))
+                conv_x<T, uint32_t><<<grid, T, bytes_lds, st>>>(C, one, xblocks, e[0], M[1], H[1], H[2], K2, plane, fx, Px, ghat, skip);
+            else
+                conv_x<T, uint64_t><<<grid, T, bytes_lds, st>>>(C, one, xblocks, e[0], M[1], H[1], H[2], K2, plane, fx, Px, ghat, skip);
+        });
+        lines(M[1], [&](auto t) {
+            constexpr int T = decltype(t)::value;
+            conv_y_inv<T><<<ygrid, T, ylds, st>>>(C, one, kblocks, e[1], H[2], K2, plane, fy, P, tgt.sparse ? tgt.range : nullptr, skip);
+        });
+        if (tgt.sparse) {
+            conv_z_targets<<<zgrid(tgt), kZThreads, sizeof(double2) * M[2], st>>>(
+                C, one, plane, H[2], K2, fz, zmagic, tgt.rows, (int)tgt.nrows, tgt.pts, outr, ldo, norm, skip);
+            BAE_HIP_CHECK(hipGetLastError());
+        } else {
+            for (int r = 0; r < nr; ++r) {
+                rows([&](auto t) {
+                    conv_z_inv<decltype(t)::value><<<gz, decltype(t)::value, ldsz, st>>>(C + r * one, e[0], e[1], e[2],
+                                                                                         plane, K2, R, fz, Pz, norm, skip);
+                });
+                if (tgt.n > 0)
+                    conv_gather<<<(unsigned)((tgt.n + 255) / 256), 256, 0, st>>>(R, tgt.at, tgt.n, outr + r * ldo);
+                BAE_HIP_CHECK(hipGetLastError());
+            }
+        }
+    }
 }
 
 }  // namespace bae

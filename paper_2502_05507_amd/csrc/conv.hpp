@@ -8,28 +8,52 @@
 
 namespace bae {
 
+struct ConvPlan;
+
+// The points of one set (sources or targets) on the convolution's box, in the set's own order.  A set with few
+// points per row (i, j) of the box (a surface) also carries them by row: its z transforms are then sums over
+// those points instead of FFTs of mostly empty rows.
+struct ConvPoints {
+    int64_t n = 0;
+    bool sparse = false;
+    void* mem = nullptr;          // holds the arrays below
+    int32_t* at = nullptr;        // box index of every point (not sparse)
+    int2* pts = nullptr;          // (z, point) sorted by row (sparse)
+    int4* rows = nullptr;         // (i, j, first point, one past the last) of the rows of every plane's range (sparse)
+    int64_t nrows = 0;
+    int2* range = nullptr;        // per plane i, the first and last row j that holds points (sparse)
+    ConvPoints() = default;
+    ConvPoints(const ConvPoints&) = delete;
+    ConvPoints& operator=(const ConvPoints&) = delete;
+    ~ConvPoints();
+    void build(const ConvPlan& cp, const PointSet& ps, hipStream_t st);
+};
+
 // v(t) = sum_s w(s) G_s(t - s) for lattice points t, s of one box, by zero-padded FFTs:
 // the box of extents e (lo its first node) is embedded in a periodic grid of M_d >= 2 e_d - 1
 // nodes, on which the kernel sampled at the wrapped offsets is a circulant (Hockney's
 // method), so the cyclic convolution equals the free-space sum at every node of the box.
 struct ConvPlan {
     int lo[3] = {0, 0, 0}, e[3] = {0, 0, 0}, M[3] = {0, 0, 0}, H[3] = {0, 0, 0};
+    int K2 = 0;                   // pitch of the half spectra along z: H2 rounded up to 128 bytes of C
+    int64_t plane = 0;            // pitch of the planes of C
     FftDev fx, fy, fz;            // transforms along the three axes (lengths M0, M1, M2)
-    double* ghat = nullptr;       // [H0][H1][H2] real: the kernel's transform on one octant
-    double* R = nullptr;          // [e0][e1][e2] real: weights in, potentials out
-    double2* C = nullptr;         // [e0][M1][M2] complex: the partly transformed grid
+    double* ghat = nullptr;       // [H0][H1][K2] real: the kernel's transform on one octant
+    double* R = nullptr;          // [e0][e1][e2] real: a dense set's weights in, potentials out (lazy)
+    double2* C = nullptr;         // [nc][e0][M1][K2] complex: the partly transformed grids of nc right-hand sides
+    int nc = 0;                   // grows to the right-hand sides asked for
     int64_t bytes = 0;
     ~ConvPlan();
     // Plans, the kernel's transform (G exactly as the FP64 sum evaluates it: the table within
     // tab_r64, the far-field expansion beyond it when the sum has one, else the full table).
     void build(const int lo_[3], const int hi_[3], const SumTables& tabs, hipStream_t st);
-    // out[t] = scale sum_s w[s] G(T_t - S_s) with sidx / tidx the box index of every source /
-    // target (ns, nt); one right-hand side; skipped while *skip is set (when given).
-    void apply(const double* w, const int32_t* sidx, int64_t ns, const int32_t* tidx, int64_t nt, double* out,
-               double scale, const int32_t* skip, hipStream_t st);
-    int64_t index(int i, int j, int k) const {   // box index of lattice node (i, j, k)
-        return ((int64_t)(i - lo[0]) * e[1] + (j - lo[1])) * e[2] + (k - lo[2]);
-    }
+    // Allocates what apply needs for these sets and right-hand sides (no launches): C holds as many of them as
+    // stay in the memory-side cache together.
+    void reserve(const ConvPoints& src, const ConvPoints& tgt, int nrhs);
+    // out[r ldo + t] = scale sum_s w[r ldw + s] G(T_t - S_s) for r < nrhs; skipped while *skip is
+    // set (when given).
+    void apply(const double* w, int64_t ldw, const ConvPoints& src, const ConvPoints& tgt, double* out, int64_t ldo,
+               int nrhs, double scale, const int32_t* skip, hipStream_t st);
 };
 
 // Smallest length >= n whose prime factors are 2, 3 and 5 (the LDS FFT's register radices).

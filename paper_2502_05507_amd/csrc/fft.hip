@@ -217,6 +217,35 @@ std::vector<int> fft_factors(int M) {
     return f;
 }
 
+std::vector<int> fft_radices(int M) {
+    static const int radix[] = {25, 24, 20, 18, 16, 15, 12, 10, 9, 8, 6, 5, 4, 3};
+    std::vector<int> best, cur;
+    int best_sum = 0;
+    // every product with non-increasing radices: the fewest, then the smallest sum (cheapest butterflies)
+    auto search = [&](auto&& self, int rest, int at, int sum) -> void {
+        if (rest == 1) {
+            if (cur.size() >= 2 && (best.empty() || cur.size() < best.size() ||
+                                    (cur.size() == best.size() && sum < best_sum))) {
+                best = cur;
+                best_sum = sum;
+            }
+            return;
+        }
+        if ((int)cur.size() == kFftMaxRadices || (!best.empty() && cur.size() >= best.size())) return;
+        for (int i = at; i < (int)(sizeof radix / sizeof radix[0]); ++i)
+            if (rest % radix[i] == 0) {
+                cur.push_back(radix[i]);
+                self(self, rest / radix[i], i, sum + radix[i]);
+                cur.pop_back();
+            }
+    };
+    search(search, M, 0, 0);
+    // odd radices first, the highest powers of two last: the first stages write R (then R R') points apart,
+    // over few of the LDS banks where that is a power of two
+    std::stable_sort(best.begin(), best.end(), [](int a, int b) { return (a & -a) < (b & -b); });
+    return best;
+}
+
 FftDev fft_plan(int M, hipStream_t st) {
     if (M < 1 || M > kFftMaxLen) throw Error{BAE_ERR_ARG, "FFT length out of range"};
     int device = 0;
@@ -230,6 +259,9 @@ FftDev fft_plan(int M, hipStream_t st) {
         h->dev.M = M;
         h->dev.nf = (int)f.size();
         for (size_t i = 0; i < f.size(); ++i) h->dev.f[i] = f[i];
+        const std::vector<int> c = fft_radices(M);
+        h->dev.nc = (int)c.size();
+        for (size_t i = 0; i < c.size(); ++i) h->dev.c[i] = c[i];
         std::vector<double2> tw(M);
         for (int t = 0; t < M; ++t) {
             // extended precision keeps every root correct to FP64 rounding

@@ -12,6 +12,7 @@ namespace bae {
 
 constexpr int kFftMaxLen = 4608;     // longest transform: two LDS buffers of it fit the 160 KB
 constexpr int kFftMaxFactors = 16;
+constexpr int kFftMaxRadices = 8;
 constexpr size_t kFftLdsBytes = 159 * 1024;   // dynamic LDS: 160 KB less 1 KB for the kernels' line tables
 
 // Complex lines of length M that one block transforms at once: c M <= 8192 points (the
@@ -28,11 +29,20 @@ struct FftDev {
     int M = 0;
     int nf = 0;
     int f[kFftMaxFactors] = {};
+    int nc = 0;                        // register radices (fft_radices), 0 where M has none
+    int c[kFftMaxRadices] = {};
     const double2* tw = nullptr;
 };
 
 // Radices of M in the order the stages apply them (4s, 2, 3s, 5s, then other primes).
 std::vector<int> fft_factors(int M);
+// The register stages run in blocks of kLineThreads threads, lines longer than 8 kLineThreads in blocks of
+// kLongThreads; a thread takes at most fft_items butterflies of a stage (8 or 16 points, or one butterfly).
+constexpr int kLineThreads = 256, kLongThreads = 512;
+constexpr int fft_items(int R, int threads) { return ((threads == kLineThreads ? 8 : 16) + R - 1) / R; }
+// M as the fewest radices among 3, 4, 5, 6, 8, 9, 10, 12, 15, 16, 18, 20, 24 and 25, at least two, in the order
+// the register stages apply them; empty where M is no such product.
+std::vector<int> fft_radices(int M);
 // The plan of length M on the current device (cached until the process ends).
 FftDev fft_plan(int M, hipStream_t st);
 // DST-I (X_k = sum_n x_n sin(pi n k / (N + 1)), unnormalised) of every line along `axis` of
