@@ -259,7 +259,7 @@ __device__ __forceinline__ void mfma_far2_block(const SumArgs<float>& a, const u
                                                 MfmaAcc<float>::V (&blk)[kTiles]) {
     const uint32_t* pxy = a.sxy + (sb + kq);
     const float* pzl = a.szl + (sb + kq);
-    const float* pw = a.w + ((int64_t)row * a.ldw + sb + kq);
+    const float* pw = a.w + ((int64_t)min(row, a.nr - 1) * a.ldw + sb + kq);
     // every counter drained here, so that the loop's waits are for its own loads only
     __builtin_amdgcn_s_waitcnt(0);
     uint32_t sxy = pxy[0];
@@ -307,7 +307,7 @@ __device__ __forceinline__ void mfma_lookup_block(const SumArgs<Real>& a, const 
     constexpr int kSteps = kSourceBlock / 4;
     const int lane = threadIdx.x & 63;
     const int bx = (int)a.sx[sb + lane], by = (int)a.sy[sb + lane], bz = (int)a.sz[sb + lane];
-    const Real* pw = a.w + ((int64_t)row * a.ldw + sb + kq);
+    const Real* pw = a.w + ((int64_t)min(row, a.nr - 1) * a.ldw + sb + kq);
     // the step's weight and its four kernel values (source 4 st + kq of the block)
     auto issue = [&](int st, Real& wv, Real (&g)[kTiles]) {
         const int from = (4 * st + kq) << 2;
@@ -452,7 +452,7 @@ __device__ __forceinline__ void mfma_tile(const SumArgs<Real>& a, const Lds<Real
         }
         for (int st = 0; st < kSourceBlock; st += 4) {
             const int s = sb + st + kq;
-            const Real wb = a.w[row * a.ldw + s];
+            const Real wb = a.w[min(row, a.nr - 1) * a.ldw + s];
             Real G[kTiles];
             if (sizeof(Real) == 8 && cls == kClassFar) {
                 const Real sx = a.sxr[s], sy = a.syr[s], sz = a.szr[s];
@@ -525,7 +525,7 @@ __device__ __forceinline__ void mfma_tile(const SumArgs<Real>& a, const Lds<Real
         for (int v = 0; v < 4; ++v) {
             const int i = sizeof(Real) == 4 ? 4 * kq + v : kq + 4 * v;
             const int t = base + 16 * j + i;
-            if (t < a.nt)
+            if (t < a.nt && row < a.nr)
                 a.part[(int64_t)row * a.ldp + (int64_t)chunk * a.nt + t] = (double)acc[j][v] - (double)comp[j][v];
         }
 }
@@ -558,6 +558,14 @@ template <typename Real>
 constexpr int mfma_threads() { return sizeof(Real) == 4 ? kSumThreads : kSumThreads / 2; }
 template <typename Real>
 constexpr int rhs4_threads() { return sizeof(Real) == 4 ? kSumThreads : kSumThreads / 2; }
+
+// Right-hand sides from which the matrix-core kernel takes a launch of up to 16 (its time does not depend on their
+// number), the 4-RHS kernel from two below it.  Times of 1 / 4 / 16 right-hand sides in us: FP64, sigma = 0, 93 / 143 /
+// 167 on the 65^3 ellipsoid and 1532 / 2041 / 2373 at 129^3; FP64, sigma > 0 (gathers), 82 / 152 / 121 and, on the 129^3
+// star, 2362 / 3915 / 3714, so that two already belong there; FP32 47 / 64 / 90, 486 / 706 / 939, star 1737 / 2625 / 2516.
+// (Launches of exactly 16, 4 and 1 took fifteen in six: 688 us where 176 do, FP64 at 65^3.)
+template <typename Real>
+int mfma_from(bool far) { return sizeof(Real) == 8 && !far ? 2 : 5; }
 
 template <typename Real>
 void launch_all(const PointSet& T, const PointSet& S, const Real* w, int nrhs, const Real* near, const Real* full,
@@ -597,28 +605,27 @@ void launch_all(const PointSet& T, const PointSet& S, const Real* w, int nrhs, c
     a.yk = (Real)(-tabs.kappa * 1.4426950408889634 / kQuant);
     a.yl = yukawa_lattice(tabs.kappa);
     a.ldp = (int64_t)plan.chunks * T.count;
-    int r = 0;
-    while (r < nrhs) {
-        const int left = nrhs - r;
+    for (int r = 0; r < nrhs;) {
         SumArgs<Real> ar = a;
         ar.w = w + (int64_t)r * a.ldw;
         ar.part = part + (int64_t)r * a.ldp;
-        const int threads = left >= 16 ? mfma_threads<Real>() : left >= 4 ? rhs4_threads<Real>() : kSumThreads;
+        const int left = nrhs - r;
         const Sched q{skip, plan.items, (uint32_t)plan.nitems, (uint32_t)((T.count + kWave - 1) / kWave), plan.counter,
                       plan.err, plan.wait_polls};
-        if (left >= 16) {
+        if (left >= mfma_from<Real>(tabs.far_field)) {
+            ar.nr = std::min(left, 16);
             if (lds_far) lgf_sum_mfma_kernel<Real, mfma_threads<Real>(), true><<<grid, mfma_threads<Real>(), 0, st>>>(ar, q);
             else lgf_sum_mfma_kernel<Real, mfma_threads<Real>(), false><<<grid, mfma_threads<Real>(), 0, st>>>(ar, q);
-            r += 16;
-        } else if (left >= 4) {
+        } else if (left >= 2) {
+            ar.nr = std::min(left, 4);
             if (lds_far) lgf_sum_kernel<Real, 4, rhs4_threads<Real>(), true><<<grid, rhs4_threads<Real>(), 0, st>>>(ar, q);
             else lgf_sum_kernel<Real, 4, rhs4_threads<Real>(), false><<<grid, rhs4_threads<Real>(), 0, st>>>(ar, q);
-            r += 4;
         } else {
+            ar.nr = 1;
             if (lds_far) lgf_sum_kernel<Real, 1, kSumThreads, true><<<grid, kSumThreads, 0, st>>>(ar, q);
             else lgf_sum_kernel<Real, 1, kSumThreads, false><<<grid, kSumThreads, 0, st>>>(ar, q);
-            r += 1;
         }
+        r += ar.nr;
         BAE_HIP_CHECK(hipGetLastError());
     }
 }
