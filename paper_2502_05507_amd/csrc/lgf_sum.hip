@@ -355,6 +355,129 @@ __device__ __forceinline__ void mfma_lookup_block(const SumArgs<Real>& a, const 
     }
 }
 
+// The FP32 kernel's table-value blocks, from the LDS or (GLOBAL) the global table: the block's 64 sources once, one per
+// lane, each step its four by a lane permutation; its weight one step ahead.  (Its registers, at four wavefronts per
+// SIMD, leave no room for the table reads of later steps; the other wavefronts cover their latency.)  16 RHS, 129^3
+// ellipsoid 933 -> 872 us, star 2512 -> 2370, against a weight loaded in its own step and branches per class inside it.
+template <bool GLOBAL>
+__device__ __forceinline__ void mfma_lookup32_block(const SumArgs<float>& a, const Lds<float>& L,
+                                                    const uint32_t (&ix)[kTiles], const uint32_t (&iy)[kTiles],
+                                                    const uint32_t (&iz)[kTiles], int sb, int row, int kq,
+                                                    MfmaAcc<float>::V (&blk)[kTiles]) {
+    const int lane = threadIdx.x & 63;
+    const int bx = (int)a.sx[sb + lane], by = (int)a.sy[sb + lane], bz = (int)a.sz[sb + lane];
+    const float* pw = a.w + ((int64_t)min(row, a.nr - 1) * a.ldw + sb + kq);
+    float w = pw[0];
+    for (int st = 0; st < kSourceBlock; st += 4) {
+        const float wn = pw[min(st + 4, kSourceBlock - 4)];
+        const int from = (st + kq) << 2;
+        const uint32_t sx = (uint32_t)__builtin_amdgcn_ds_bpermute(from, bx);
+        const uint32_t sy = (uint32_t)__builtin_amdgcn_ds_bpermute(from, by);
+        const uint32_t sz = (uint32_t)__builtin_amdgcn_ds_bpermute(from, bz);
+        uint32_t lo[kTiles], th[kTiles], tm[kTiles];
+#pragma unroll
+        for (int j = 0; j < kTiles; ++j) {
+            const uint32_t da = absdiff_v(ix[j], sx), db = absdiff_v(iy[j], sy), dc = absdiff_v(iz[j], sz);
+            lo[j] = min3u(da, db, dc);
+            th[j] = *(const uint32_t*)((const char*)L.tet + max3u(da, db, dc));
+            tm[j] = *(const uint32_t*)((const char*)L.tri + med3u(da, db, dc));
+        }
+        float G[kTiles];
+#pragma unroll
+        for (int j = 0; j < kTiles; ++j) {
+            const uint32_t o = th[j] + tm[j] + lo[j];
+            G[j] = GLOBAL ? global_value(a.full_tab, o) : lds_value(L, o);
+        }
+#pragma unroll
+        for (int j = 0; j < kTiles; ++j) blk[j] = MfmaAcc<float>::mma(G[j], w, blk[j]);
+        w = wn;
+    }
+}
+
+// FP32 blocks with pairs on both sides of the LDS radius: per pair the table or the far field.  (Both values for every
+// pair and a selection, or a branch per step of four tiles, took the 129^3 star's sum from 2.37 to 2.59 and 2.51 ms: the
+// targets and sources are compact patches, so a tile's pairs mostly lie on one side and the other is skipped.)
+__device__ __forceinline__ void mfma_mixed32_block(const SumArgs<float>& a, const Lds<float>& L,
+                                                   const uint32_t (&ix)[kTiles], const uint32_t (&iy)[kTiles],
+                                                   const uint32_t (&iz)[kTiles], int sb, int row, int kq,
+                                                   MfmaAcc<float>::V (&blk)[kTiles]) {
+    const int lane = threadIdx.x & 63;
+    const uint32_t tab_q = (uint32_t)(kQuant * a.tab_r);
+    const int bx = (int)a.sx[sb + lane], by = (int)a.sy[sb + lane], bz = (int)a.sz[sb + lane];
+    const float* pw = a.w + ((int64_t)min(row, a.nr - 1) * a.ldw + sb + kq);
+    float w = pw[0];
+    for (int st = 0; st < kSourceBlock; st += 4) {
+        const float wn = pw[min(st + 4, kSourceBlock - 4)];
+        const int from = (st + kq) << 2;
+        const uint32_t sx = (uint32_t)__builtin_amdgcn_ds_bpermute(from, bx);
+        const uint32_t sy = (uint32_t)__builtin_amdgcn_ds_bpermute(from, by);
+        const uint32_t sz = (uint32_t)__builtin_amdgcn_ds_bpermute(from, bz);
+        float G[kTiles];
+#pragma unroll
+        for (int j = 0; j < kTiles; ++j) {
+            const uint32_t da = absdiff_v(ix[j], sx), db = absdiff_v(iy[j], sy), dc = absdiff_v(iz[j], sz);
+            if (max3u(da, db, dc) <= tab_q) {
+                G[j] = lds_value(L, table_offset(L, da, db, dc));
+            } else {
+                // |d| components of the integer offsets, exact in FP32
+                const float dx = (float)da, dy = (float)db, dz = (float)dc;
+                G[j] = a.yukawa ? far_field_yukawa<float>(dx * dx, dy * dy, dz * dz, a.kq, a.yk)
+                                : far_field<float>(dx * dx, dy * dy, dz * dz);
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < kTiles; ++j) blk[j] = MfmaAcc<float>::mma(G[j], w, blk[j]);
+        w = wn;
+    }
+}
+
+// FP64 far blocks (sigma = 0, q = 4 in registers) and, MIXED, blocks with pairs on both sides of the LDS radius.
+// The block's sources come once, one per lane, and its weights four steps ahead, so that a step waits on no load
+// (loaded per step, with two wavefronts per SIMD to cover the latency, the 16-RHS sum took 178 us on the 65^3 ellipsoid,
+// 5% of such pairs, and 2379 at 129^3, 61%; here 156 and 2126).  The offsets are integer differences, exact in FP64.
+template <bool MIXED>
+__device__ __forceinline__ void mfma_far64_block(const SumArgs<double>& a, const Lds<double>& L,
+                                                 const uint32_t (&ix)[kTiles], const uint32_t (&iy)[kTiles],
+                                                 const uint32_t (&iz)[kTiles], int sb, int row, int kq,
+                                                 MfmaAcc<double>::V (&blk)[kTiles]) {
+    constexpr int kAhead = 4, kSteps = kSourceBlock / 4;
+    const int lane = threadIdx.x & 63;
+    const int bx = (int)a.sx[sb + lane], by = (int)a.sy[sb + lane], bz = (int)a.sz[sb + lane];
+    const double* pw = a.w + ((int64_t)min(row, a.nr - 1) * a.ldw + sb + kq);
+    const uint32_t tab_q = (uint32_t)(kQuant * a.tab_r);
+    double w[kAhead];
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) w[u] = pw[4 * u];
+    for (int s0 = 0; s0 < kSteps; s0 += kAhead) {
+        double wn[kAhead];
+        const int n0 = min(s0 + kAhead, kSteps - kAhead);
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) wn[u] = pw[4 * (n0 + u)];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            const int from = (4 * (s0 + u) + kq) << 2;
+            const int sx = __builtin_amdgcn_ds_bpermute(from, bx), sy = __builtin_amdgcn_ds_bpermute(from, by),
+                      sz = __builtin_amdgcn_ds_bpermute(from, bz);
+            double G[kTiles];
+#pragma unroll
+            for (int j = 0; j < kTiles; ++j) {
+                const double dx = (double)((int)ix[j] - sx), dy = (double)((int)iy[j] - sy), dz = (double)((int)iz[j] - sz);
+                if constexpr (MIXED) {
+                    const uint32_t da = absdiff_v(ix[j], sx), db = absdiff_v(iy[j], sy), dc = absdiff_v(iz[j], sz);
+                    G[j] = max3u(da, db, dc) <= tab_q ? lds_value(L, table_offset(L, da, db, dc))
+                                                      : far_field<double>(dx * dx, dy * dy, dz * dz);
+                } else {
+                    G[j] = far_field<double>(dx * dx, dy * dy, dz * dz);
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < kTiles; ++j) blk[j] = MfmaAcc<double>::mma(G[j], w[u], blk[j]);
+        }
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) w[u] = wn[u];
+    }
+}
+
 template <typename Real>
 __device__ __forceinline__ void mfma_tile(const SumArgs<Real>& a, const Lds<Real>& L, int tile, int chunk) {
     using V = typename MfmaAcc<Real>::V;
@@ -386,7 +509,6 @@ __device__ __forceinline__ void mfma_tile(const SumArgs<Real>& a, const Lds<Real
     hx = wave_max(hx);
     hy = wave_max(hy);
     hz = wave_max(hz);
-    const uint32_t tab_q = (uint32_t)(kQuant * a.tab_r);
 
     V acc[kTiles], comp[kTiles];
 #pragma unroll
@@ -423,88 +545,18 @@ __device__ __forceinline__ void mfma_tile(const SumArgs<Real>& a, const Lds<Real
                 else mfma_far2_block<false>(a, txy, tzl, sb, row, kq, blk);
             }
         }
-        // FP64 table-value blocks have loops of their own (the FP32 kernel's registers, at four
-        // wavefronts per SIMD, leave no room for them: its table, gather and mixed blocks take
-        // the step loop below)
-        bool done = false;
         if constexpr (sizeof(Real) == 8) {
-            if (cls == kClassTable) {
-                mfma_lookup_block<Real, false>(a, L, ix, iy, iz, sb, row, kq, blk);
-                done = true;
-            } else if (cls == kClassGather || (cls == kClassMixed && !a.far_ok)) {
+            if (cls == kClassTable) mfma_lookup_block<Real, false>(a, L, ix, iy, iz, sb, row, kq, blk);
+            else if (cls == kClassGather || (cls == kClassMixed && !a.far_ok))
                 mfma_lookup_block<Real, true>(a, L, ix, iy, iz, sb, row, kq, blk);
-                done = true;
-            }
-        } else {
-            done = cls == kClassFar2;
-        }
-        if (!done) {
-        // Table, gather and mixed blocks take the block's 64 integer source coordinates once,
-        // one per lane, and each step its four by a lane permutation (outside the
-        // vector-memory counter).
-        const bool by_lane = !(sizeof(Real) == 8 && cls == kClassFar);
-        int bxq = 0, byq = 0, bzq = 0;
-        if (by_lane) {
-            const int lane = threadIdx.x & 63;
-            bxq = (int)a.sx[sb + lane];
-            byq = (int)a.sy[sb + lane];
-            bzq = (int)a.sz[sb + lane];
-        }
-        for (int st = 0; st < kSourceBlock; st += 4) {
-            const int s = sb + st + kq;
-            const Real wb = a.w[min(row, a.nr - 1) * a.ldw + s];
-            Real G[kTiles];
-            if (sizeof(Real) == 8 && cls == kClassFar) {
-                const Real sx = a.sxr[s], sy = a.syr[s], sz = a.szr[s];
-                // the targets' coordinates converted here (registers kept for the loops above)
-                if (a.yukawa) {
-#pragma unroll
-                    for (int j = 0; j < kTiles; ++j) {
-                        const Real dx = (Real)ix[j] - sx, dy = (Real)iy[j] - sy, dz = (Real)iz[j] - sz;
-                        G[j] = far_field_yukawa<Real>(dx * dx, dy * dy, dz * dz, a.kq, a.yk);
-                    }
-                } else {
-#pragma unroll
-                    for (int j = 0; j < kTiles; ++j) {
-                        const Real dx = (Real)ix[j] - sx, dy = (Real)iy[j] - sy, dz = (Real)iz[j] - sz;
-                        G[j] = far_field<Real>(dx * dx, dy * dy, dz * dz);
-                    }
-                }
-            } else {
-                const int from = (st + kq) << 2;
-                const uint32_t sx = (uint32_t)__builtin_amdgcn_ds_bpermute(from, bxq);
-                const uint32_t sy = (uint32_t)__builtin_amdgcn_ds_bpermute(from, byq);
-                const uint32_t sz = (uint32_t)__builtin_amdgcn_ds_bpermute(from, bzq);
-                if (cls == kClassTable) {
-#pragma unroll
-                    for (int j = 0; j < kTiles; ++j)
-                        G[j] = lds_value(L, table_offset(L, absdiff_v(ix[j], sx), absdiff_v(iy[j], sy),
-                                                         absdiff_v(iz[j], sz)));
-                } else if (cls == kClassGather) {
-#pragma unroll
-                    for (int j = 0; j < kTiles; ++j)
-                        G[j] = global_value(a.full_tab, table_offset(L, absdiff_v(ix[j], sx), absdiff_v(iy[j], sy),
-                                                                      absdiff_v(iz[j], sz)));
-                } else {
-#pragma unroll
-                    for (int j = 0; j < kTiles; ++j) {
-                        const uint32_t da = absdiff_v(ix[j], sx), db = absdiff_v(iy[j], sy), dc = absdiff_v(iz[j], sz);
-                        if (max3u(da, db, dc) <= tab_q) {
-                            G[j] = lds_value(L, table_offset(L, da, db, dc));
-                        } else if (a.far_ok) {
-                            // |d| components of the integer offsets, exact in the kernel's precision
-                            const Real dx = (Real)da, dy = (Real)db, dz = (Real)dc;
-                            G[j] = a.yukawa ? far_field_yukawa<Real>(dx * dx, dy * dy, dz * dz, a.kq, a.yk)
-                                            : far_field<Real>(dx * dx, dy * dy, dz * dz);
-                        } else {
-                            G[j] = global_value(a.full_tab, table_offset(L, da, db, dc));
-                        }
-                    }
-                }
-            }
-#pragma unroll
-            for (int j = 0; j < kTiles; ++j) blk[j] = MfmaAcc<Real>::mma(G[j], wb, blk[j]);
-        }
+            else if (cls == kClassMixed) mfma_far64_block<true>(a, L, ix, iy, iz, sb, row, kq, blk);
+            else mfma_far64_block<false>(a, L, ix, iy, iz, sb, row, kq, blk);
+        } else if (cls == kClassMixed && a.far_ok) {
+            mfma_mixed32_block(a, L, ix, iy, iz, sb, row, kq, blk);
+        } else if (cls == kClassTable) {
+            mfma_lookup32_block<false>(a, L, ix, iy, iz, sb, row, kq, blk);
+        } else if (cls != kClassFar2) {   // gather, and mixed without a far field: the global table holds every offset
+            mfma_lookup32_block<true>(a, L, ix, iy, iz, sb, row, kq, blk);
         }
         // FP32: fold the block's sums into the running accumulators, compensated (Kahan):
         // 4 VALU instructions per accumulator element (Neumaier's branch-free form takes 8)
