@@ -31,7 +31,9 @@ int guard(const std::function<void()>& fn);
 namespace {
 
 constexpr int kT = 256;       // threads per block (all batched kernels)
-constexpr int kSlice = 2048;  // elements per dot-product slice
+constexpr int kSlice = 1024;  // elements per dot-product slice
+constexpr int kDotWaves = 8;  // wavefronts of a dot-product block: one Krylov vector each at a time
+constexpr int kHChunk = 512;  // Gram-Schmidt coefficients staged in LDS at a time
 
 // Device descriptor of one problem of the batch.
 struct BProb {
@@ -42,7 +44,8 @@ struct BProb {
     const int32_t *tq, *tp, *tpos;
     const double* tw;
     int n, nt, ns_pad, chunks, nslices, m;
-    double *V, *H, *cs, *sn, *g, *hist, *beta, *hA, *hB, *nrm, *dpart, *y;
+    int nrblk;             // row blocks of kT (slices of ||w||^2)
+    double *V, *H, *cs, *sn, *g, *hist, *beta, *hA, *hB, *nrm, *dpart, *npart, *y;
     int32_t *done, *kdone;
     double *b, *x, *r, *tmp, *ug, *upg;
     void* w;
@@ -75,9 +78,10 @@ __device__ inline int owner(const int64_t* off, int np, int64_t g) {
 // src: 0 -> V[k], 1 -> x
 template <typename Real>
 __global__ void b_weights(const BProb* __restrict__ P, const int64_t* __restrict__ off, int np, int64_t total,
-                          int src, int use_done, const int32_t* __restrict__ sel) {
+                          int src, int use_done, const int32_t* __restrict__ sel, int32_t* __restrict__ next_item) {
     const int64_t gi = (int64_t)blockIdx.x * kT + threadIdx.x;
     if (gi >= total) return;
+    if (gi == 0) *next_item = 0;   // the work counter of the sum that follows
     const int p = owner(off, np, gi);
     if (sel && !sel[p]) return;
     const BProb& q = P[p];
@@ -96,32 +100,42 @@ __global__ void b_weights(const BProb* __restrict__ P, const int64_t* __restrict
 // Persistent LGF sum over (problem, 1024-target tile, source chunk) items: each of the 16
 // wavefronts of a workgroup takes one 64-target tile of the item.  The LDS table is
 // restaged only when an item needs another table (sigma > 0 problems each have their own;
-// every sigma = 0 problem shares one) or a larger prefix of it.
+// every sigma = 0 problem shares one) or a larger prefix of it.  A workgroup's first item is its own index, each
+// further one comes from a counter (drawn while the item before is evaluated): items differ in cost (tables, partly
+// filled tiles, converged problems), and in a fixed round-robin the last workgroups set the time (352 us per sum of 24
+// problems of 32 to 64 nodes per axis; drawn 297).
 template <typename Real>
 __global__ __launch_bounds__(kSumThreads) void b_lgf_sum(const BProb* __restrict__ P, const Item* __restrict__ items,
-                                                         int nitems, int use_done, const int32_t* __restrict__ sel) {
+                                                         int nitems, int use_done, const int32_t* __restrict__ sel,
+                                                         int32_t* __restrict__ next_item) {
     __shared__ __align__(16) char lds[lds_bytes<Real, false>()];
+    __shared__ int32_t drawn[2];
     const Lds<Real> L = lds_layout<Real, false>(lds);
     fill_index<Real>(L, kMaxR);
     const Real* cur = nullptr;
     int cur_r = -1;
     const int wave = threadIdx.x >> 6;
-    for (int it = blockIdx.x; it < nitems; it += gridDim.x) {
+    int it = blockIdx.x;
+    for (int turn = 0; it < nitems; ++turn) {
+        if (threadIdx.x == 0) drawn[turn & 1] = (int32_t)gridDim.x + atomicAdd(next_item, 1);
         const Item w = items[it];
         const BProb& q = P[w.p];
-        if ((use_done && q.done[0]) || (sel && !sel[w.p])) continue;   // uniform over the block
-        const SumArgs<Real>& a = sum_args<Real>(q);
-        if (a.near_tab != cur || a.tab_r > cur_r) {
-            __syncthreads();
-            stage_table(L.tab, a.near_tab, (a.tab_r + 1) * (a.tab_r + 2) * (a.tab_r + 3) / 6);
-            __syncthreads();
-            cur = a.near_tab;
-            cur_r = a.tab_r;
+        if (!((use_done && q.done[0]) || (sel && !sel[w.p]))) {   // uniform over the block
+            const SumArgs<Real>& a = sum_args<Real>(q);
+            if (a.near_tab != cur || a.tab_r > cur_r) {
+                __syncthreads();
+                stage_table(L.tab, a.near_tab, (a.tab_r + 1) * (a.tab_r + 2) * (a.tab_r + 3) / 6);
+                __syncthreads();
+                cur = a.near_tab;
+                cur_r = a.tab_r;
+            }
+            const int tile = w.tile * (kSumThreads / kWave) + wave;
+            // every problem here is small: its chunk fits the scalar cache only while the
+            // item's wavefronts walk it together, so no rotation
+            if (tile * kWave < a.nt) sum_tile<Real, 1, false>(a, L, tile, w.chunk);
         }
-        const int tile = w.tile * (kSumThreads / kWave) + wave;
-        // every problem here is small: its chunk fits the scalar cache only while the
-        // item's wavefronts walk it together, so no rotation
-        if (tile * kWave < a.nt) sum_tile<Real, 1, false>(a, L, tile, w.chunk);
+        __syncthreads();
+        it = drawn[turn & 1];   // (the slot is written again two turns on, past the next barrier)
     }
 }
 
@@ -140,7 +154,21 @@ __global__ void b_closure(const BProb* __restrict__ P, const int64_t* __restrict
     if (i >= q.n) return;
     const int64_t a = q.tq[i], b = q.tp[i];
     double va = 0.0, vb = 0.0;
-    for (int c = 0; c < q.chunks; ++c) {
+    int c = 0;
+    for (; c + 8 <= q.chunks; c += 8) {   // 16 loads in flight, added in order
+        double pa[8], pb[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            pa[u] = q.part[(int64_t)(c + u) * q.nt + a];
+            pb[u] = q.part[(int64_t)(c + u) * q.nt + b];
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            va += pa[u];
+            vb += pb[u];
+        }
+    }
+    for (; c < q.chunks; ++c) {
         va += q.part[(int64_t)c * q.nt + a];
         vb += q.part[(int64_t)c * q.nt + b];
     }
@@ -178,114 +206,185 @@ __device__ inline double block_sum(double v, double* sh) {
     return s;
 }
 
-// mode 0: dpart[j][slice] = V[j] . V[k+1], j <= k;  mode 1: dpart[0] = V[k+1] . V[k+1];
-// mode 2: dpart[0] = vec . vec with vec = b (sel 0) or r (sel 1)
-__global__ __launch_bounds__(kT) void b_dots(const BProb* __restrict__ P, const int2* __restrict__ slices, int nitems,
-                                             int mode, int sel, int use_done) {
+// dpart[slice] = vec . vec with vec = b (sel 0) or r (sel 1)
+__global__ __launch_bounds__(kT) void b_norm_slices(const BProb* __restrict__ P, const int2* __restrict__ slices, int sel) {
     __shared__ double sh[kT / 64];
     const int2 w = slices[blockIdx.x];
     const BProb& q = P[w.x];
-    if (use_done && q.done[0]) return;
-    const int k = q.ctl->k;
-    if (mode != 2 && (k < 0 || k >= q.m)) return;
     const int64_t lo = (int64_t)w.y * kSlice, hi = min((int64_t)q.n, lo + kSlice);
-    if (mode == 0) {
-        const double* y = q.V + (int64_t)(k + 1) * q.n;
-        for (int j = 0; j <= k; ++j) {
-            const double* x = q.V + (int64_t)j * q.n;
-            double acc = 0.0;
-            for (int64_t i = lo + threadIdx.x; i < hi; i += kT) acc = fma(x[i], y[i], acc);
-            const double s = block_sum(acc, sh);
-            if (threadIdx.x == 0) q.dpart[(int64_t)j * q.nslices + w.y] = s;
-        }
-    } else {
-        const double* y = mode == 1 ? q.V + (int64_t)(k + 1) * q.n : (sel == 0 ? q.b : q.r);
-        double acc = 0.0;
-        for (int64_t i = lo + threadIdx.x; i < hi; i += kT) acc = fma(y[i], y[i], acc);
-        const double s = block_sum(acc, sh);
-        if (threadIdx.x == 0) q.dpart[w.y] = s;
-    }
-}
-
-// h[j] = sum over slices; dest 0 -> hA, 1 -> hB, 2 -> nrm (one value)
-__global__ void b_dots_finalize(const BProb* __restrict__ P, int np, int dest, int nj_mode, int use_done) {
-    const int p = blockIdx.x;
-    const BProb& q = P[p];
-    if (use_done && q.done[0]) return;
-    const int k = q.ctl->k;
-    if (nj_mode == 0 && (k < 0 || k >= q.m)) return;
-    const int nj = nj_mode == 0 ? k + 1 : 1;
-    double* h = dest == 0 ? q.hA : dest == 1 ? q.hB : q.nrm;
-    for (int j = threadIdx.x; j < nj; j += blockDim.x) {
-        double s = 0.0;
-        for (int b = 0; b < q.nslices; ++b) s += q.dpart[(int64_t)j * q.nslices + b];
-        h[j] = s;
-    }
-}
-
-__global__ void b_subtract(const BProb* __restrict__ P, const int64_t* __restrict__ off, int np, int64_t total,
-                           int which) {
-    const int64_t gi = (int64_t)blockIdx.x * kT + threadIdx.x;
-    if (gi >= total) return;
-    const int p = owner(off, np, gi);
-    const BProb& q = P[p];
-    const int k = q.ctl->k;
-    if (q.done[0] || k < 0 || k >= q.m) return;
-    const int64_t i = gi - off[p];
-    if (i >= q.n) return;
-    const double* h = which == 0 ? q.hA : q.hB;
+    const double* y = sel == 0 ? q.b : q.r;
     double acc = 0.0;
-    for (int j = 0; j <= k; ++j) acc = fma(h[j], q.V[(int64_t)j * q.n + i], acc);
-    q.V[(int64_t)(k + 1) * q.n + i] -= acc;
+    for (int64_t i = lo + threadIdx.x; i < hi; i += kT) acc = fma(y[i], y[i], acc);
+    const double s = block_sum(acc, sh);
+    if (threadIdx.x == 0) q.dpart[w.y] = s;
 }
 
-__global__ void b_normalize(const BProb* __restrict__ P, const int64_t* __restrict__ off, int np, int64_t total) {
-    const int64_t gi = (int64_t)blockIdx.x * kT + threadIdx.x;
-    if (gi >= total) return;
-    const int p = owner(off, np, gi);
-    const BProb& q = P[p];
-    const int k = q.ctl->k;
-    if (q.done[0] || k < 0 || k >= q.m) return;
-    const double nr = sqrt(q.nrm[0]);
-    if (gi - off[p] >= q.n) return;
-    if (nr > 0.0) q.V[(int64_t)(k + 1) * q.n + gi - off[p]] /= nr;
-}
-
-// One thread per problem: Givens update of column k, residual estimate, convergence flag,
-// then the problem's own step counter advances (every other kernel of the iteration has
-// read it by now).
-__global__ void b_givens(const BProb* __restrict__ P, int np, int two_pass) {
+// nrm = the sum of those slices
+__global__ void b_norm_finalize(const BProb* __restrict__ P, int np) {
     const int p = blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= np) return;
     const BProb& q = P[p];
+    double s = 0.0;
+    for (int b = 0; b < q.nslices; ++b) s += q.dpart[b];
+    q.nrm[0] = s;
+}
+
+// dpart[j][slice] = V[j] . V[k+1] over the slice, j <= k.  A wavefront holds the slice of V[k+1] in registers and takes
+// every kDotWaves-th vector, its 16 loads in flight together.  (One block of four wavefronts per slice, all on one
+// vector at a time with two barriers each, took 48 us per call on 24 problems of 32 to 64 nodes per axis; here 10.)
+__global__ __launch_bounds__(kDotWaves * 64) void b_dots(const BProb* __restrict__ P, const int2* __restrict__ slices) {
+    constexpr int U = kSlice / 64;
+    const int2 w = slices[blockIdx.x];
+    const BProb& q = P[w.x];
+    if (q.done[0]) return;
+    const int k = q.ctl->k;
+    if (k < 0 || k >= q.m) return;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int lo = w.y * kSlice + lane, n = q.n;
+    const double* yv = q.V + (int64_t)(k + 1) * n;
+    // beyond the vector's end: its last element, times zero
+    int at[U];
+    double y[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        at[u] = min(lo + 64 * u, n - 1);
+        y[u] = yv[at[u]];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+        if (lo + 64 * u >= n) y[u] = 0.0;
+    for (int j = wave; j <= k; j += kDotWaves) {
+        const double* xv = q.V + (int64_t)j * n;
+        double x[U], acc[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int u = 0; u < U; ++u) x[u] = xv[at[u]];
+#pragma unroll
+        for (int u = 0; u < U; ++u) acc[u & 3] = fma(x[u], y[u], acc[u & 3]);
+        double s = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+        for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+        if (lane == 0) q.dpart[(int64_t)j * q.nslices + w.y] = s;
+    }
+}
+
+// V[k+1] -= sum_{j <= k} h[j] V[j] on a row block of one problem, h[j] the sum of its slices (kept in hA or hB by the
+// problem's first block); the last pass also leaves the block's part of ||V[k+1]||^2.
+__global__ __launch_bounds__(kT) void b_subtract(const BProb* __restrict__ P, const int2* __restrict__ rblocks, int pass,
+                                                 int last) {
+    __shared__ double hs[kHChunk];
+    __shared__ double sh[kT / 64];
+    const int2 w = rblocks[blockIdx.x];
+    const BProb& q = P[w.x];
+    if (q.done[0]) return;
+    const int k = q.ctl->k;
+    if (k < 0 || k >= q.m) return;
+    const int n = q.n, i = w.y * kT + threadIdx.x, ns = q.nslices;
+    double* h = pass == 0 ? q.hA : q.hB;
+    double acc = 0.0;
+    for (int j0 = 0; j0 <= k; j0 += kHChunk) {
+        const int j1 = min(k + 1, j0 + kHChunk);
+        __syncthreads();
+        for (int j = j0 + (int)threadIdx.x; j < j1; j += kT) {
+            const double* d = q.dpart + (int64_t)j * ns;
+            double s = 0.0;
+            for (int b = 0; b < ns; ++b) s += d[b];
+            hs[j - j0] = s;
+            if (w.y == 0) h[j] = s;
+        }
+        __syncthreads();
+        if (i < n) {
+            const double* x = q.V + (int64_t)j0 * n + i;
+            int j = 0;
+            for (; j + 8 <= j1 - j0; j += 8) {
+                double v[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) v[u] = x[(int64_t)(j + u) * n];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) acc = fma(hs[j + u], v[u], acc);
+            }
+            for (; j < j1 - j0; ++j) acc = fma(hs[j], x[(int64_t)j * n], acc);
+        }
+    }
+    double v2 = 0.0;
+    if (i < n) {
+        double* y = q.V + (int64_t)(k + 1) * n + i;
+        const double v = *y - acc;
+        *y = v;
+        v2 = v * v;
+    }
+    if (!last) return;
+    const double s = block_sum(v2, sh);
+    if (threadIdx.x == 0) q.npart[w.y] = s;
+}
+
+// The sum of a problem's ||w||^2 slices, by every wavefront alike.
+__device__ inline double wave_norm2(const BProb& q) {
+    double t = 0.0;
+    for (int b = threadIdx.x & 63; b < q.nrblk; b += 64) t += q.npart[b];
+    for (int o = 32; o > 0; o >>= 1) t += __shfl_xor(t, o, 64);
+    return t;
+}
+
+__global__ __launch_bounds__(kT) void b_normalize(const BProb* __restrict__ P, const int2* __restrict__ rblocks) {
+    const int2 w = rblocks[blockIdx.x];
+    const BProb& q = P[w.x];
+    if (q.done[0]) return;
+    const int k = q.ctl->k;
+    if (k < 0 || k >= q.m) return;
+    const double nr = sqrt(wave_norm2(q));
+    const int i = w.y * kT + threadIdx.x;
+    if (i < q.n && nr > 0.0) q.V[(int64_t)(k + 1) * q.n + i] /= nr;
+}
+
+// One block per problem: Givens update of column k, residual estimate, convergence flag, then the problem's own step
+// counter advances (every other kernel of the iteration has read it by now).  The rotations are a sequential chain:
+// its operands are staged in LDS (from global memory, by one thread per problem, a call took 32 us).
+constexpr int kGivensChunk = 256;
+__global__ __launch_bounds__(64) void b_givens(const BProb* __restrict__ P, int two_pass) {
+    __shared__ double hc[kGivensChunk], cc[kGivensChunk], sc[kGivensChunk];
+    const BProb& q = P[blockIdx.x];
     const int k = q.ctl->k;
     if (q.done[0]) return;
     if (k < 0 || k >= q.m || k >= q.ctl->maxit) {
-        q.done[0] = 1;
+        if (threadIdx.x == 0) q.done[0] = 1;
         return;
     }
     double* h = q.H + (int64_t)k * (q.m + 1);
-    for (int i = 0; i <= k; ++i) h[i] = two_pass ? q.hA[i] + q.hB[i] : q.hA[i];
-    const double hk1 = sqrt(q.nrm[0]);
-    for (int i = 0; i < k; ++i) {
-        const double a = h[i], b = h[i + 1];
-        h[i] = q.cs[i] * a + q.sn[i] * b;
-        h[i + 1] = -q.sn[i] * a + q.cs[i] * b;
+    auto hval = [&](int i) { return two_pass ? q.hA[i] + q.hB[i] : q.hA[i]; };
+    const double hk1 = sqrt(wave_norm2(q));
+    double x = hval(0);   // the entry the next rotation takes first (thread 0)
+    for (int i0 = 0; i0 < k; i0 += kGivensChunk) {
+        const int i1 = min(k, i0 + kGivensChunk);
+        __syncthreads();
+        for (int i = i0 + (int)threadIdx.x; i < i1; i += 64) {
+            hc[i - i0] = hval(i + 1);
+            cc[i - i0] = q.cs[i];
+            sc[i - i0] = q.sn[i];
+        }
+        __syncthreads();
+        if (threadIdx.x == 0)
+            for (int i = i0; i < i1; ++i) {
+                const double y = hc[i - i0], c = cc[i - i0], sn = sc[i - i0];
+                hc[i - i0] = c * x + sn * y;
+                x = -sn * x + c * y;
+            }
+        __syncthreads();
+        for (int i = i0 + (int)threadIdx.x; i < i1; i += 64) h[i] = hc[i - i0];
     }
-    const double a = h[k], b = hk1;
-    const double rr = hypot(a, b);
+    if (threadIdx.x != 0) return;
+    const double rr = hypot(x, hk1);
     if (rr == 0.0) {
         q.done[0] = 1;
         q.kdone[0] = k;
         return;
     }
-    q.cs[k] = a / rr;
-    q.sn[k] = b / rr;
+    const double c = x / rr, sn = hk1 / rr, gk = q.g[k];
+    q.cs[k] = c;
+    q.sn[k] = sn;
     h[k] = rr;
     h[k + 1] = 0.0;
-    q.g[k + 1] = -q.sn[k] * q.g[k];
-    q.g[k] = q.cs[k] * q.g[k];
-    const double est = fabs(q.g[k + 1]) / q.beta[0];
+    q.g[k + 1] = -sn * gk;
+    q.g[k] = c * gk;
+    const double est = fabs(-sn * gk) / q.beta[0];
     q.hist[k] = est;
     q.kdone[0] = k + 1;
     if (est <= q.ctl->tol || hk1 == 0.0 || k + 1 >= q.m || k + 1 >= q.ctl->maxit) q.done[0] = 1;
@@ -328,17 +427,22 @@ __global__ void b_init(const BProb* __restrict__ P, const int64_t* __restrict__ 
     q.V[i] = bnorm > 0.0 ? r0[i] / bnorm : 0.0;
 }
 
-// thread per problem (mask[p] = 1): y = R^-1 g over the first kdone[p] columns
-__global__ void b_backsolve(const BProb* __restrict__ P, int np, const int32_t* __restrict__ mask) {
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= np || !mask[p]) return;
+// y = R^-1 g over the first kdone[p] columns, one block per problem (mask[p] = 1): column by column, the rows above in
+// parallel.  (One thread per problem took 460 us at 40 columns.)
+__global__ __launch_bounds__(64) void b_backsolve(const BProb* __restrict__ P, const int32_t* __restrict__ mask) {
+    const int p = blockIdx.x;
+    if (!mask[p]) return;
     const BProb& q = P[p];
     const int kk = q.kdone[0];
+    for (int j = threadIdx.x; j < kk; j += 64) q.y[j] = q.g[j];
+    __syncthreads();
     for (int i = kk - 1; i >= 0; --i) {
-        double acc = q.g[i];
-        for (int j = i + 1; j < kk; ++j) acc -= q.H[(int64_t)j * (q.m + 1) + i] * q.y[j];
-        const double d = q.H[(int64_t)i * (q.m + 1) + i];
-        q.y[i] = d != 0.0 ? acc / d : 0.0;
+        const double* col = q.H + (int64_t)i * (q.m + 1);
+        const double d = col[i], yi = d != 0.0 ? q.y[i] / d : 0.0;
+        __syncthreads();
+        for (int j = threadIdx.x; j < i; j += 64) q.y[j] -= col[j] * yi;
+        if (threadIdx.x == 0) q.y[i] = yi;
+        __syncthreads();
     }
 }
 
@@ -384,9 +488,9 @@ struct BatchEngine {
     bool own_stream = false;
     std::vector<bae_ctx*> ctx;
     int np = 0;
-    DevMem probs, off_src, off_row, off_tgt, slices, items, ctl_init, mask, arena, gi, gd;
+    DevMem probs, off_src, off_row, off_tgt, slices, rblocks, next_item, items, ctl_init, mask, arena, gi, gd;
     int64_t tot_src = 0, tot_row = 0, tot_tgt = 0;
-    int nslices_total = 0, nitems = 0;
+    int nslices_total = 0, nrblk_total = 0, nitems = 0;
     int blk_per_chunk = 8, grid_mult = 1, n_cu = 256;
     std::vector<BProb> hp;
     hipGraph_t graph[2] = {nullptr, nullptr};
@@ -428,10 +532,10 @@ void build_layout(BatchEngine* b) {
         BAE_HIP_CHECK(hipHostMalloc((void**)&b->pinned, sizeof(int32_t) * b->pinned_cap, hipHostMallocDefault));
     }
     std::vector<int64_t> osrc(b->np), orow(b->np), otgt(b->np);
-    std::vector<int2> sl;
+    std::vector<int2> sl, rb;
     std::vector<Item> it;
     int64_t arena = 0;
-    std::vector<int64_t> part_at(b->np), dpart_at(b->np);
+    std::vector<int64_t> part_at(b->np), dpart_at(b->np), npart_at(b->np);
     for (int p = 0; p < b->np; ++p) {
         bae_ctx* c = b->ctx[p];
         BProb& q = b->hp[p];
@@ -444,6 +548,8 @@ void build_layout(BatchEngine* b) {
         q.chunks = (int)((c->S.ps.nblk + b->blk_per_chunk - 1) / b->blk_per_chunk);
         q.nslices = (int)((c->ngm + kSlice - 1) / kSlice);
         for (int s = 0; s < q.nslices; ++s) sl.push_back(make_int2(p, s));
+        q.nrblk = (int)((c->ngm + kT - 1) / kT);
+        for (int s = 0; s < q.nrblk; ++s) rb.push_back(make_int2(p, s));
         const int tiles = (int)((c->nT + kSumThreads - 1) / kSumThreads);
         for (int t = 0; t < tiles; ++t)
             for (int ch = 0; ch < q.chunks; ++ch) it.push_back(Item{p, t, ch, 0});
@@ -451,12 +557,15 @@ void build_layout(BatchEngine* b) {
         arena += (int64_t)q.chunks * c->nT;
         dpart_at[p] = arena;
         arena += (int64_t)(c->K.m + 1) * q.nslices;
+        npart_at[p] = arena;
+        arena += q.nrblk;
     }
     // largest problems' items first keeps the persistent grid busy to the end
     std::stable_sort(it.begin(), it.end(), [&](const Item& x, const Item& y) {
         return b->ctx[x.p]->nT * b->ctx[x.p]->nS > b->ctx[y.p]->nT * b->ctx[y.p]->nS;
     });
     b->arena.alloc(sizeof(double) * arena);
+    b->next_item.alloc(sizeof(int32_t));
     b->ctl_init.alloc(sizeof(Ctl) * b->np);
     b->mask.alloc(sizeof(int32_t) * b->np);
     b->gi.alloc(sizeof(int32_t) * b->np);
@@ -466,6 +575,7 @@ void build_layout(BatchEngine* b) {
         BProb& q = b->hp[p];
         q.part = b->arena.as<double>() + part_at[p];
         q.dpart = b->arena.as<double>() + dpart_at[p];
+        q.npart = b->arena.as<double>() + npart_at[p];
         q.ctl = c->ctl.as<Ctl>();
         q.rowptr = c->B.rowptr;
         q.col = c->B.col;
@@ -544,11 +654,13 @@ void build_layout(BatchEngine* b) {
         q.s32.yl = yukawa_lattice(c->tabs.kappa);
     }
     b->nslices_total = (int)sl.size();
+    b->nrblk_total = (int)rb.size();
     b->nitems = (int)it.size();
     upload(b->off_src, osrc, st);
     upload(b->off_row, orow, st);
     upload(b->off_tgt, otgt, st);
     upload(b->slices, sl, st);
+    upload(b->rblocks, rb, st);
     upload(b->items, it, st);
     upload(b->probs, b->hp, st);
     BAE_HIP_CHECK(hipStreamSynchronize(st));
@@ -560,14 +672,15 @@ void apply_all(BatchEngine* b, int prec, int src, int dst, int use_done, const i
     hipStream_t st = b->stream;
     const BProb* P = b->probs.as<BProb>();
     const unsigned grid = (unsigned)std::max(1, std::min(b->nitems, b->grid_mult * b->n_cu));
+    int32_t* next = b->next_item.as<int32_t>();
     if (prec == BAE_PREC_FP64) {
         b_weights<double><<<nblocks(b->tot_src), kT, 0, st>>>(P, b->off_src.as<int64_t>(), b->np, b->tot_src, src,
-                                                              use_done, sel);
-        b_lgf_sum<double><<<grid, kSumThreads, 0, st>>>(P, b->items.as<Item>(), b->nitems, use_done, sel);
+                                                              use_done, sel, next);
+        b_lgf_sum<double><<<grid, kSumThreads, 0, st>>>(P, b->items.as<Item>(), b->nitems, use_done, sel, next);
     } else {
         b_weights<float><<<nblocks(b->tot_src), kT, 0, st>>>(P, b->off_src.as<int64_t>(), b->np, b->tot_src, src,
-                                                             use_done, sel);
-        b_lgf_sum<float><<<grid, kSumThreads, 0, st>>>(P, b->items.as<Item>(), b->nitems, use_done, sel);
+                                                             use_done, sel, next);
+        b_lgf_sum<float><<<grid, kSumThreads, 0, st>>>(P, b->items.as<Item>(), b->nitems, use_done, sel, next);
     }
     if (dst >= 0)
         b_closure<<<nblocks(b->tot_row), kT, 0, st>>>(P, b->off_row.as<int64_t>(), b->np, b->tot_row, dst, use_done,
@@ -579,8 +692,8 @@ void apply_all(BatchEngine* b, int prec, int src, int dst, int use_done, const i
 void norms(BatchEngine* b, int sel) {
     hipStream_t st = b->stream;
     const BProb* P = b->probs.as<BProb>();
-    b_dots<<<b->nslices_total, kT, 0, st>>>(P, b->slices.as<int2>(), b->nslices_total, 2, sel, 0);
-    b_dots_finalize<<<b->np, 64, 0, st>>>(P, b->np, 2, 1, 0);
+    b_norm_slices<<<b->nslices_total, kT, 0, st>>>(P, b->slices.as<int2>(), sel);
+    b_norm_finalize<<<(b->np + 63) / 64, 64, 0, st>>>(P, b->np);
     BAE_HIP_CHECK(hipGetLastError());
 }
 
@@ -610,19 +723,16 @@ void gmres_iteration(BatchEngine* b, int prec) {
     hipStream_t st = b->stream;
     const BProb* P = b->probs.as<BProb>();
     apply_all(b, prec, 0, 0, 1);
-    const int64_t* orow = b->off_row.as<int64_t>();
+    const int2 *slices = b->slices.as<int2>(), *rblocks = b->rblocks.as<int2>();
     // CGS2 in FP64; one pass in the FP32 inner solves, whose results an exact FP64 residual
     // checks (as in the single-context solver)
     const int passes = prec == BAE_PREC_FP64 ? 2 : 1;
     for (int pass = 0; pass < passes; ++pass) {
-        b_dots<<<b->nslices_total, kT, 0, st>>>(P, b->slices.as<int2>(), b->nslices_total, 0, 0, 1);
-        b_dots_finalize<<<b->np, 64, 0, st>>>(P, b->np, pass, 0, 1);
-        b_subtract<<<nblocks(b->tot_row), kT, 0, st>>>(P, orow, b->np, b->tot_row, pass);
+        b_dots<<<b->nslices_total, kDotWaves * 64, 0, st>>>(P, slices);
+        b_subtract<<<b->nrblk_total, kT, 0, st>>>(P, rblocks, pass, pass + 1 == passes);
     }
-    b_dots<<<b->nslices_total, kT, 0, st>>>(P, b->slices.as<int2>(), b->nslices_total, 1, 0, 1);
-    b_dots_finalize<<<b->np, 64, 0, st>>>(P, b->np, 2, 1, 1);
-    b_normalize<<<nblocks(b->tot_row), kT, 0, st>>>(P, orow, b->np, b->tot_row);
-    b_givens<<<(b->np + 63) / 64, 64, 0, st>>>(P, b->np, passes == 2);
+    b_normalize<<<b->nrblk_total, kT, 0, st>>>(P, rblocks);
+    b_givens<<<b->np, 64, 0, st>>>(P, passes == 2);
     BAE_HIP_CHECK(hipGetLastError());
 }
 
@@ -678,7 +788,7 @@ void batch_finish(BatchEngine* b, const std::vector<int32_t>& mask, bool accumul
     if (b->np == 0) return;
     hipStream_t st = b->stream;
     BAE_HIP_CHECK(hipMemcpyAsync(b->mask.p, mask.data(), sizeof(int32_t) * b->np, hipMemcpyHostToDevice, st));
-    b_backsolve<<<(b->np + 63) / 64, 64, 0, st>>>(b->probs.as<BProb>(), b->np, b->mask.as<int32_t>());
+    b_backsolve<<<b->np, 64, 0, st>>>(b->probs.as<BProb>(), b->mask.as<int32_t>());
     b_update_x<<<nblocks(b->tot_row), kT, 0, st>>>(b->probs.as<BProb>(), b->off_row.as<int64_t>(), b->np, b->tot_row,
                                                    accumulate ? 1 : 0, b->mask.as<int32_t>());
     BAE_HIP_CHECK(hipGetLastError());
