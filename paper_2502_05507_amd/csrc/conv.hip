@@ -522,7 +522,7 @@ __global__ void conv_kernel_grid(double2* __restrict__ g, int M0, int M1, int M2
         const int hi = max(a, max(b, c)), lo = min(a, min(b, c)), mid = a + b + c - hi - lo;
         if (hi > tab_r && far_ok) {
             const double X = (double)(kQuant * a), Y = (double)(kQuant * b), Z = (double)(kQuant * c);
-            v = lgfdev::far_field<double>(X * X, Y * Y, Z * Z);
+            v = lgfdev::far_field<double>(X, Y, Z);
         } else if (hi <= full_r) {
             v = tab[(int64_t)hi * (hi + 1) * (hi + 2) / 6 + (int64_t)mid * (mid + 1) / 2 + lo];
         } else {

@@ -110,15 +110,6 @@ __device__ __forceinline__ void far_pairs4(uint32_t t, uint32_t s0, uint32_t s1,
         : "v"(t), "s"(s0), "s"(s1), "s"(s2), "s"(s3), "v"(Z[0]), "v"(Z[1]), "v"(Z[2]), "v"(Z[3]));
 }
 
-// 1/sqrt(x) of a positive finite FP64 square sum: the hardware estimate and one Newton
-// step, whose relative error is about 1.5 e0^2 for an estimate error e0 (no special
-// cases to handle, unlike the library rsqrt).
-__device__ __forceinline__ double rsqrt_pos(double x) {
-    const double y = __builtin_amdgcn_rsq(x);
-    const double e = fma(-x * y, y, 1.0);
-    return fma(0.5 * y, e, y);
-}
-
 // The same for four targets t_k of one lane against one source s (both per lane).
 __device__ __forceinline__ void far_pairs4v(const uint32_t (&t)[4], uint32_t s, const float (&Z)[4], float (&r2)[4],
                                             float (&m)[4]) {
@@ -141,24 +132,31 @@ __device__ __forceinline__ void far_pairs4v(const uint32_t (&t)[4], uint32_t s, 
         : "v"(t[0]), "v"(t[1]), "v"(t[2]), "v"(t[3]), "v"(s), "v"(Z[0]), "v"(Z[1]), "v"(Z[2]), "v"(Z[3]));
 }
 
-// FP64: q = 4 from the squared quantised offset components (all >= 0, not all 0); relative
-// error <= 6.6e-11 beyond the far-field gap.
-__device__ __forceinline__ double far_field_q4(double X, double Y, double Z) {
-    const double r2 = X + Y + Z;
-    const double yz = Y * Z;
-    const double e2 = fma(X, Y + Z, yz);
-    const double e3 = X * yz;
-    const double rinv = rsqrt_pos(r2);
-    const double rho = rinv * rinv;
-    const double rho2 = rho * rho;
-    const double x = e2 * rho2;
-    const double y = e3 * rho2 * rho;
-    double d = fma(D3, y, fma(x, fma(x, D2, D1), D0));
-    const double f = fma(y, fma(F5, x, F4), fma(x, fma(x, fma(x, F3, F2), F1), F0));
+// FP64: q = 4 from the quantised offset components (not all 0); relative error <= 6.6e-11
+// beyond the far-field gap.  The arithmetic bounds the FP64 sums, so it is written for its
+// instruction count (31 and the estimate; 129^3 ellipsoid 1403 us with 34, 1324 so): with z = Z/r^2 and w = X Y/r^4, the symmetric
+// functions e2/r^4 and e3/r^6 of the squares are z (1 - z) + w and z w; and the Newton step of
+// the inverse square root, y (3 - r^2 y^2)/2 (relative error about 1.5 e0^2 for an estimate error
+// e0, no special cases to handle), shares y^2 and its bracket with 1/r^2 and leaves its half
+// to the coefficients.
+__device__ __forceinline__ double far_field_q4(double dx, double dy, double dz) {
+    const double xy = dx * dy, Z = dz * dz;
+    const double r2 = fma(dx, dx, dy * dy) + Z;
+    const double y0 = __builtin_amdgcn_rsq(r2);
+    const double rho0 = y0 * y0;
+    const double g = fma(-r2, rho0, 3.0);        // 1/r = y0 g / 2
+    const double rho = fma(rho0, g, -rho0);      // 1/r^2 = rho0 (2 - r^2 rho0)
+    const double z = Z * rho, b = xy * rho;
+    const double w = b * b;
+    const double x = fma(z, 1.0 - z, w);
+    const double y = z * w;
+    double d = fma(0.5 * D3, y, fma(x, fma(x, 0.5 * D2, 0.5 * D1), 0.5 * D0));
+    const double f = fma(y, fma(0.5 * F5, x, 0.5 * F4),
+                         fma(x, fma(x, fma(x, 0.5 * F3, 0.5 * F2), 0.5 * F1), 0.5 * F0));
     d = fma(rho, f, d);
-    const double c = fma(C2, x, C1);
-    const double B = fma(rho, fma(rho, d, c), C0);
-    return rinv * B;
+    const double c = fma(0.5 * C2, x, 0.5 * C1);
+    const double B = fma(rho, fma(rho, d, c), 0.5 * C0);
+    return (y0 * g) * B;
 }
 
 // sigma > 0 (s = kappa^2 in lattice units): the same Fourier-symbol expansion with
@@ -241,10 +239,11 @@ __device__ __forceinline__ float far_field_yukawa_lattice(float r2, float Z, flo
     return __builtin_amdgcn_exp2f(arg) * rinv;
 }
 
+// sigma = 0, from the quantised offset components.
 template <typename Real>
-__device__ __forceinline__ Real far_field(Real X, Real Y, Real Z) {
-    if constexpr (sizeof(Real) == 4) return far_field_q2(X, Y, Z);
-    else return far_field_q4(X, Y, Z);
+__device__ __forceinline__ Real far_field(Real dx, Real dy, Real dz) {
+    if constexpr (sizeof(Real) == 4) return far_field_q2(dx * dx, dy * dy, dz * dz);
+    else return far_field_q4(dx, dy, dz);
 }
 
 // |a - b| of two non-negative coordinates in one instruction.  The second operand is a
@@ -600,12 +599,16 @@ __device__ __forceinline__ void sum_tile(const SumArgs<Real>& a, const Lds<Real>
             if (a.yukawa) far2_block<Real, NR, true>(a, txy, tzl, sb, acc);
             else far2_block<Real, NR, false>(a, txy, tzl, sb, acc);
         } else if ((cls == kClassFar || cls == kClassFar2) && !a.yukawa) {
-            for (int s0 = sb; s0 < sb + kSourceBlock; s0 += U) {
-                const Step<Real, NR> st = load_step<Real, NR, false, true>(a, s0);
+            // (one RHS, 129^3 ellipsoid, 59% of the pairs here: 1324 us with 4 sources a step, 1296 with 8, whose scalar
+            // loads are waited for half as often; the next step's loads in flight take the registers of the
+            // coefficients: 1372)
+            constexpr int UF = NR == 1 ? 8 : 4;
+            for (int s0 = sb; s0 < sb + kSourceBlock; s0 += UF) {
+                const Step<Real, NR, UF> st = load_step<Real, NR, false, true, false, UF>(a, s0);
 #pragma unroll
-                for (int u = 0; u < U; ++u) {
+                for (int u = 0; u < UF; ++u) {
                     const Real dx = fx - st.xr[u], dy = fy - st.yr[u], dz = fz - st.zr[u];
-                    const Real G = far_field<Real>(dx * dx, dy * dy, dz * dz);
+                    const Real G = far_field<Real>(dx, dy, dz);
 #pragma unroll
                     for (int r = 0; r < NR; ++r) acc[r].add(G * st.w[r][u]);
                 }
@@ -643,7 +646,7 @@ __device__ __forceinline__ void sum_tile(const SumArgs<Real>& a, const Lds<Real>
                     } else if (a.far_ok) {
                         const Real dx = fx - st.xr[u], dy = fy - st.yr[u], dz = fz - st.zr[u];
                         G = a.yukawa ? far_field_yukawa<Real>(dx * dx, dy * dy, dz * dz, a.kq, a.yk)
-                                     : far_field<Real>(dx * dx, dy * dy, dz * dz);
+                                     : far_field<Real>(dx, dy, dz);
                     } else {
                         G = global_value(a.full_tab, table_offset(L, da, db, dc));
                     }

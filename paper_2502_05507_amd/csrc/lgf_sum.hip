@@ -182,7 +182,7 @@ __global__ void lgf_eval_kernel(const int32_t* __restrict__ off, int64_t count, 
         } else if (yukawa) {
             out[i] = (double)far_field_yukawa<Real>(X * X, Y * Y, Z * Z, kq, yk);
         } else {
-            out[i] = (double)far_field<Real>(X * X, Y * Y, Z * Z);
+            out[i] = (double)far_field<Real>(X, Y, Z);
         }
         return;
     }
@@ -422,7 +422,7 @@ __device__ __forceinline__ void mfma_mixed32_block(const SumArgs<float>& a, cons
                 // |d| components of the integer offsets, exact in FP32
                 const float dx = (float)da, dy = (float)db, dz = (float)dc;
                 G[j] = a.yukawa ? far_field_yukawa<float>(dx * dx, dy * dy, dz * dz, a.kq, a.yk)
-                                : far_field<float>(dx * dx, dy * dy, dz * dz);
+                                : far_field<float>(dx, dy, dz);
             }
         }
 #pragma unroll
@@ -465,9 +465,9 @@ __device__ __forceinline__ void mfma_far64_block(const SumArgs<double>& a, const
                 if constexpr (MIXED) {
                     const uint32_t da = absdiff_v(ix[j], sx), db = absdiff_v(iy[j], sy), dc = absdiff_v(iz[j], sz);
                     G[j] = max3u(da, db, dc) <= tab_q ? lds_value(L, table_offset(L, da, db, dc))
-                                                      : far_field<double>(dx * dx, dy * dy, dz * dz);
+                                                      : far_field<double>(dx, dy, dz);
                 } else {
-                    G[j] = far_field<double>(dx * dx, dy * dy, dz * dz);
+                    G[j] = far_field<double>(dx, dy, dz);
                 }
             }
 #pragma unroll
