@@ -43,6 +43,17 @@ std::shared_ptr<Table> get_table(int device, double s, int R, hipStream_t st) {
     t->d32.alloc(sizeof(float) * E);
     lgf_table_generate(s, R, t->d64.as<double>(), st);
     launch_to_float(t->d64.as<double>(), t->d32.as<float>(), E, st);
+    if (table_bricked(s, R)) {
+        DevMem prefix;
+        t->b64.alloc(sizeof(double) * brick_entries(R));
+        prefix.alloc(sizeof(double) * table_size(kLdsRadius64));
+        table_bricks(t->d64.as<double>(), R, t->b64.as<double>(), st);
+        BAE_HIP_CHECK(hipMemcpyAsync(prefix.p, t->d64.p, sizeof(double) * table_size(kLdsRadius64),
+                                     hipMemcpyDeviceToDevice, st));
+        BAE_HIP_CHECK(hipStreamSynchronize(st));
+        std::swap(t->d64.p, prefix.p);
+        std::swap(t->d64.bytes, prefix.bytes);
+    }
     BAE_HIP_CHECK(hipStreamSynchronize(st));
     (*g_tables)[{device, key}] = t;
     return t;
@@ -695,7 +706,8 @@ bae_ctx* create_context(const bae_grid& gridv, const bae_options* opt, Geometry&
         c->table = get_table(c->device, c->s, R, st);
         c->tabs.near64 = c->table->d64.as<double>();
         c->tabs.near32 = c->table->d32.as<float>();
-        c->tabs.full64 = c->table->d64.as<double>();
+        c->tabs.bricked = table_bricked(c->s, c->table->R);
+        c->tabs.full64 = c->tabs.bricked ? c->table->b64.as<double>() : c->table->d64.as<double>();
         c->tabs.full32 = c->table->d32.as<float>();
         c->tabs.full_r = c->table->R;
         const int need = std::max(G.max_offset, kFarGap);
@@ -707,7 +719,7 @@ bae_ctx* create_context(const bae_grid& gridv, const bae_options* opt, Geometry&
         // only where it matches this context's own exact table everywhere (FP64 keeps the table)
         c->tabs.kappa = std::sqrt(c->s);
         if (!far && c->tabs.full_r > c->tabs.tab_r32) {
-            c->tabs.yukawa_err = yukawa_check(c->table->d64.as<double>(), c->tabs.full_r, c->tabs.tab_r32,
+            c->tabs.yukawa_err = yukawa_check(c->tabs.full64, c->tabs.bricked, c->tabs.full_r, c->tabs.tab_r32,
                                               c->tabs.kappa, st);
             c->tabs.yukawa32 = c->tabs.yukawa_err <= kYukawaTolerance;
         }
@@ -838,7 +850,11 @@ int64_t estimate_context_bytes(const Geometry& G, double s, const bae_options* o
     b += 4 * ngm * mr * 8 + 2 * nT * mr * 8;                                           // b, x, r, tmp, u_p, u_gamma
     const int64_t pr = std::min<int64_t>(kRecycleDefault, m);
     b += (2 * ngm + (int64_t)m * dot_blocks(ngm)) * pr * mr * 8;                      // refined solves' recycling
-    if (s > 0.0) b += table_size(std::max(32, G.max_offset)) * 12;                     // its own table
+    if (s > 0.0) {                                                                     // its own table
+        const int R = std::max(32, G.max_offset);
+        b += table_size(R) * 4 +
+             8 * (table_bricked(s, R) ? brick_entries(R) + table_size(kLdsRadius64) : table_size(R));
+    }
     return b;
 }
 

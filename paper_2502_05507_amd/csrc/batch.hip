@@ -111,7 +111,7 @@ __global__ __launch_bounds__(kSumThreads) void b_lgf_sum(const BProb* __restrict
     __shared__ __align__(16) char lds[lds_bytes<Real, false>()];
     __shared__ int32_t drawn[2];
     const Lds<Real> L = lds_layout<Real, false>(lds);
-    fill_index<Real>(L, kMaxR);
+    fill_index<Real, false>(L, kMaxR);
     const Real* cur = nullptr;
     int cur_r = -1;
     const int wave = threadIdx.x >> 6;

@@ -63,8 +63,10 @@ struct Table {
     int device = 0;
     double s = 0.0;
     int R = 0;
-    DevMem d64, d32;
+    DevMem d64, d32;   // sorted tables: FP64 of radius min(R, kLdsRadius64) where b64 holds the rest
+    DevMem b64;        // sigma > 0, R > kLdsRadius64: the FP64 table in bricks
 };
+inline bool table_bricked(double s, int R) { return s > 0.0 && R > kLdsRadius64; }
 
 std::shared_ptr<Table> get_table(int device, double s, int R, hipStream_t st);
 int guard(const std::function<void()>& fn);

@@ -511,7 +511,8 @@ __global__ __launch_bounds__(THREADS, 4) void conv_z_inv(const double2* __restri
 // The kernel sampled at the wrapped offsets of the padded grid (full M0 x M1 x M2, complex with
 // zero imaginary part), G exactly as the FP64 sum evaluates it.
 __global__ void conv_kernel_grid(double2* __restrict__ g, int M0, int M1, int M2, int e0, int e1, int e2,
-                                 const double* __restrict__ tab, int tab_r, int full_r, int far_ok) {
+                                 const double* __restrict__ tab, int bricked, int tab_r, int full_r,
+                                 int far_ok) {
     const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (q >= (int64_t)M0 * M1 * M2) return;
     const int i = (int)(q / ((int64_t)M1 * M2)), j = (int)((q / M2) % M1), k = (int)(q % M2);
@@ -524,7 +525,7 @@ __global__ void conv_kernel_grid(double2* __restrict__ g, int M0, int M1, int M2
             const double X = (double)(kQuant * a), Y = (double)(kQuant * b), Z = (double)(kQuant * c);
             v = lgfdev::far_field<double>(X, Y, Z);
         } else if (hi <= full_r) {
-            v = tab[(int64_t)hi * (hi + 1) * (hi + 2) / 6 + (int64_t)mid * (mid + 1) / 2 + lo];
+            v = lgfdev::full_entry(tab, bricked != 0, hi, mid, lo);
         } else {
             v = __builtin_nan("");
         }
@@ -754,8 +755,8 @@ void ConvPlan::build(const int lo_[3], const int hi_[3], const SumTables& tabs, 
     device_alloc((void**)&g, sizeof(double2) * full);
     try {
         conv_kernel_grid<<<(unsigned)((full + 255) / 256), 256, 0, st>>>(g, M[0], M[1], M[2], e[0], e[1], e[2],
-                                                                          tabs.full64, tabs.tab_r64, tabs.full_r,
-                                                                          tabs.far64() ? 1 : 0);
+                                                                          tabs.full64, tabs.bricked ? 1 : 0, tabs.tab_r64,
+                                                                          tabs.full_r, tabs.far64() ? 1 : 0);
         BAE_HIP_CHECK(hipGetLastError());
         kernel_pass(g, (int64_t)M[0] * M[1], 1, M[2], 1, fz, st);                              // rows
         kernel_pass(g, (int64_t)M[0] * M[2], M[2], (int64_t)M[1] * M[2], M[2], fy, st);        // columns of every plane

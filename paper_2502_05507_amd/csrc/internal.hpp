@@ -47,6 +47,21 @@ std::vector<int32_t> morton_order(const int32_t* pts, int64_t count, const int l
 
 // ------------------------------------------------------------------ LGF table (device)
 int64_t table_size(int R);
+
+// The FP64 sum's global table (sigma > 0, offsets beyond the LDS radius) in bricks of 128 bytes, one cache line: 2 x 2 x 4
+// neighbouring entries in (hi, mid, lo), the bricks in sorted order.  What bounds those sums is the L1's line accesses: 64
+// pairs of 16 neighbouring targets and a few sources touch 51 lines of the sorted table, whose rows run along lo only, and
+// 43 of this one, with half the requests to the L2 (16 right-hand sides on the 129^3 star: 3782 -> 3343 us).  Entry (hi, mid, lo) lies at byte
+// brick_hi(hi) + brick_mid(mid) + brick_lo(lo); bricks on the diagonal hold entries that are never read.
+// Row (H, M) of bricks, H = hi / 2 and M = mid / 2, has M / 2 + 1 of them (lo <= 2 M + 1), so that
+// floor((M + 1)^2 / 4) precede it in its plane H, and N (N + 2) (2 N - 1) / 24, N = H + 1, (rounded down) that plane.
+__host__ __device__ constexpr int64_t brick_count(int64_t H) { return (H + 1) * (H + 3) * (2 * H + 1) / 24; }
+__host__ __device__ constexpr uint32_t brick_hi(int hi) { return (uint32_t)(128 * brick_count(hi / 2)) + 64u * (hi & 1); }
+__host__ __device__ constexpr uint32_t brick_mid(int mid) {
+    return 128u * ((uint32_t)((mid / 2 + 1) * (mid / 2 + 1)) / 4u) + 32u * (mid & 1);
+}
+__host__ __device__ constexpr uint32_t brick_lo(int lo) { return 128u * (uint32_t)(lo / 4) + 8u * (lo & 3); }
+__host__ __device__ constexpr int64_t brick_entries(int R) { return 16 * brick_count(R / 2 + 1); }   // radius R
 // FP64 table G_s for 0<=a<=b<=c<=R into out (device), on stream.
 void lgf_table_generate(double s, int R, double* out, hipStream_t stream);
 // The same with no allocation: scratch in a static device array (R <= kNoAllocMaxR);
@@ -115,7 +130,8 @@ struct PointSet {
 struct SumTables {
     const double* near64 = nullptr;          // table prefix staged in LDS (device)
     const float* near32 = nullptr;
-    const double* full64 = nullptr;          // full table (device), radius full_r
+    const double* full64 = nullptr;          // full table (device), radius full_r: in bricks when bricked
+    bool bricked = false;                    // sigma > 0 and full_r > kLdsRadius64
     const float* full32 = nullptr;
     int full_r = 0;
     int tab_r64 = 0, tab_r32 = 0;            // LDS radii: min(build radius, full_r)
@@ -148,6 +164,9 @@ void plan_sum(const PointSet& T, const PointSet& S, const SumTables& tabs, SumPl
 int lgf_sum_chunks(int64_t nt, int64_t nblk);
 int lgf_sum_grid(int device);    // workgroups of the persistent sum kernels
 
+// The FP64 table of radius R in bricks (out: brick_entries(R)).
+void table_bricks(const double* table, int R, double* out, hipStream_t st);
+
 // v[r][t] (partials per source chunk: part[r][chunk][t]) = sum_s w[r][s] G(T_t - S_s).
 // w is FP64 when prec == BAE_PREC_FP64, FP32 otherwise.  Returns number of chunks used.
 // skip: optional device flag; when it is set at launch time the kernels do nothing.
@@ -158,6 +177,6 @@ void lgf_eval_launch(const int32_t* off, int64_t count, double* out, int prec, c
                      hipStream_t st);
 // Largest relative difference between the sigma > 0 far-field form (evaluated in FP64) and
 // the exact table over every offset with max-norm in (from_r, R]; host result.
-double yukawa_check(const double* table, int R, int from_r, double kappa, hipStream_t st);
+double yukawa_check(const double* table, bool bricked, int R, int from_r, double kappa, hipStream_t st);
 
 }  // namespace bae

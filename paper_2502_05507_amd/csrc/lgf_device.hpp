@@ -283,21 +283,29 @@ struct Lds {
     Real* tab;            // table prefix, radius tab_r
     uint32_t* tet;
     uint32_t* tri;
+    uint32_t* bhi;        // FP64, sigma > 0: brick_hi and brick_mid up to the global table's radius
+    uint32_t* bmid;
 };
 
 // One LDS allocation, index arrays first: every LDS address the lookups form is then a
 // register plus a constant below 64 KB, which ds_read takes as its immediate offset.
 template <typename Real, bool FAR>
-constexpr int idx_len() {   // index array length: > the largest radius indexed, 16-byte multiple
-    return ((FAR ? tab_radius<Real, FAR>() : kMaxR) + 4) / 4 * 4;
+constexpr bool has_bricks() { return sizeof(Real) == 8 && !FAR; }
+constexpr int padded_len(int r) { return (r + 4) / 4 * 4; }   // > the largest radius indexed, 16-byte multiple
+template <typename Real, bool FAR>
+constexpr int idx_len() { return padded_len(FAR || sizeof(Real) == 8 ? tab_radius<Real, FAR>() : kMaxR); }
+template <typename Real, bool FAR>
+constexpr int brick_len() { return has_bricks<Real, FAR>() ? padded_len(kMaxR) : 0; }
+template <typename Real, bool FAR>
+constexpr int lds_bytes() {
+    return 2 * (idx_len<Real, FAR>() + brick_len<Real, FAR>()) * 4 + tab_entries<Real, FAR>() * (int)sizeof(Real);
 }
 template <typename Real, bool FAR>
-constexpr int lds_bytes() { return 2 * idx_len<Real, FAR>() * 4 + tab_entries<Real, FAR>() * (int)sizeof(Real); }
-template <typename Real, bool FAR>
 __device__ __forceinline__ Lds<Real> lds_layout(char* base) {
-    constexpr int n = idx_len<Real, FAR>();
+    constexpr int n = idx_len<Real, FAR>(), m = brick_len<Real, FAR>();
     static_assert(lds_bytes<Real, FAR>() <= 160 * 1024, "LDS of one gfx950 compute unit");
-    return Lds<Real>{(Real*)(base + 2 * n * 4), (uint32_t*)base, (uint32_t*)(base + n * 4)};
+    uint32_t* i = (uint32_t*)base;
+    return Lds<Real>{(Real*)(i + 2 * (n + m)), i, i + n, i + 2 * n, i + 2 * n + m};
 }
 
 // Byte offset of G(d) in a sorted table from the quantised |d| components.
@@ -318,13 +326,46 @@ template <typename Real>
 __device__ __forceinline__ Real global_value(const Real* __restrict__ full, uint32_t off) {
     return *(const Real*)((const char*)full + off);
 }
-
+// The index arrays of an LDS (GLOBAL: global table) lookup, and the byte offset from what they hold.  (FP64: the global
+// table is in bricks.)
+template <typename Real, bool GLOBAL>
+__device__ __forceinline__ uint32_t index_hi(const Lds<Real>& L, uint32_t hi) {
+    return *(const uint32_t*)((const char*)(GLOBAL && sizeof(Real) == 8 ? L.bhi : L.tet) + hi);
+}
+template <typename Real, bool GLOBAL>
+__device__ __forceinline__ uint32_t index_mid(const Lds<Real>& L, uint32_t mid) {
+    return *(const uint32_t*)((const char*)(GLOBAL && sizeof(Real) == 8 ? L.bmid : L.tri) + mid);
+}
+template <typename Real, bool GLOBAL>
+__device__ __forceinline__ uint32_t index_sum(uint32_t th, uint32_t tm, uint32_t lo) {   // lo quantised
+    if constexpr (sizeof(Real) == 4) return th + tm + lo;
+    else if constexpr (GLOBAL) return th + tm + 2u * lo + 96u * (lo >> 4);   // brick_lo(lo / kQuant)
+    else return th + tm + 2u * lo;
+}
 template <typename Real>
+__device__ __forceinline__ uint32_t global_offset(const Lds<Real>& L, uint32_t a, uint32_t b, uint32_t c) {
+    return index_sum<Real, true>(index_hi<Real, true>(L, max3u(a, b, c)), index_mid<Real, true>(L, med3u(a, b, c)),
+                                 min3u(a, b, c));
+}
+// Entry (hi, mid, lo) of a full FP64 table, sorted or in bricks.
+__device__ __forceinline__ double full_entry(const double* __restrict__ tab, bool bricked, int hi, int mid, int lo) {
+    if (bricked) return *(const double*)((const char*)tab + (brick_hi(hi) + brick_mid(mid) + brick_lo(lo)));
+    return tab[(int64_t)hi * (hi + 1) * (hi + 2) / 6 + (int64_t)mid * (mid + 1) / 2 + lo];
+}
+
+// The index arrays up to radius idx_r.  FAR as in the layout.
+template <typename Real, bool FAR>
 __device__ __forceinline__ void fill_index(const Lds<Real>& L, int idx_r) {
-    for (int h = threadIdx.x; h <= idx_r; h += blockDim.x) {
+    for (int h = threadIdx.x; h <= min(idx_r, idx_len<Real, FAR>() - 1); h += blockDim.x) {
         const uint32_t u = (uint32_t)h;
         L.tet[h] = (uint32_t)sizeof(Real) * (u * (u + 1) * (u + 2) / 6);
         L.tri[h] = (uint32_t)sizeof(Real) * (u * (u + 1) / 2);
+    }
+    if constexpr (has_bricks<Real, FAR>()) {
+        for (int h = threadIdx.x; h <= idx_r; h += blockDim.x) {
+            L.bhi[h] = brick_hi(h);
+            L.bmid[h] = brick_mid(h);
+        }
     }
 }
 
@@ -356,10 +397,10 @@ __device__ __forceinline__ void stage_table(Real* dst, const Real* __restrict__ 
 }
 
 // Fill the LDS table prefix (radius tab_r) and the index arrays up to radius idx_r.
-template <typename Real>
+template <typename Real, bool FAR>
 __device__ __forceinline__ void fill_lds(const Lds<Real>& L, const Real* __restrict__ src, int tab_r, int idx_r) {
     stage_table(L.tab, src, (tab_r + 1) * (tab_r + 2) * (tab_r + 3) / 6);
-    fill_index<Real>(L, idx_r);
+    fill_index<Real, FAR>(L, idx_r);
 }
 
 __device__ __forceinline__ int wave_min(int v) {
@@ -409,7 +450,7 @@ struct SumArgs {
     int64_t ldw;
     int nr;                           // right-hand sides of the launch (a kernel's further ones repeat the last, unstored)
     const Real* near_tab;             // table prefix staged in LDS (radius tab_r)
-    const Real* full_tab;             // full table (sigma > 0): radius full_r
+    const Real* full_tab;             // full table (sigma > 0): radius full_r; FP64: in bricks
     int tab_r;                        // LDS table radius used (<= the kernel's tab_radius)
     int full_r;
     int far_ok;                       // a far field is valid beyond far_gap (and beyond tab_r)
@@ -492,13 +533,13 @@ __device__ __forceinline__ void lookup_step(const Lds<Real>& L, const Real* __re
     uint32_t th[U], tm[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-        th[u] = *(const uint32_t*)((const char*)L.tet + hi[u]);
-        tm[u] = *(const uint32_t*)((const char*)L.tri + mid[u]);
+        th[u] = index_hi<Real, GLOBAL>(L, hi[u]);
+        tm[u] = index_mid<Real, GLOBAL>(L, mid[u]);
     }
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-        const uint32_t off = sizeof(Real) == 4 ? th[u] + tm[u] + lo[u] : th[u] + tm[u] + 2u * lo[u];
+        const uint32_t off = index_sum<Real, GLOBAL>(th[u], tm[u], lo[u]);
         G[u] = GLOBAL ? global_value(full, off) : lds_value(L, off);
     }
     __builtin_amdgcn_sched_barrier(0);
@@ -648,7 +689,7 @@ __device__ __forceinline__ void sum_tile(const SumArgs<Real>& a, const Lds<Real>
                         G = a.yukawa ? far_field_yukawa<Real>(dx * dx, dy * dy, dz * dz, a.kq, a.yk)
                                      : far_field<Real>(dx, dy, dz);
                     } else {
-                        G = global_value(a.full_tab, table_offset(L, da, db, dc));
+                        G = global_value(a.full_tab, global_offset(L, da, db, dc));
                     }
 #pragma unroll
                     for (int r = 0; r < NR; ++r) acc[r].add(G * st.w[r][u]);

@@ -159,14 +159,14 @@ __global__ __launch_bounds__(THREADS) void lgf_sum_kernel(const SumArgs<Real> a,
     const Lds<Real> L = lds_layout<Real, FAR>(lds);
     __shared__ ItemRing ring;
     ring_init(&ring);
-    fill_lds(L, a.near_tab, a.tab_r, FAR ? a.tab_r : a.full_r);
+    fill_lds<Real, FAR>(L, a.near_tab, a.tab_r, FAR ? a.tab_r : a.full_r);
     __syncthreads();
     for_each_item(q, &ring, [&](uint32_t tile, uint32_t chunk) { sum_tile<Real, NR>(a, L, (int)tile, (int)chunk); });
 }
 
 template <typename Real>
 __global__ void lgf_eval_kernel(const int32_t* __restrict__ off, int64_t count, const Real* __restrict__ tab,
-                                int tab_r, int full_r, int far_ok, int yukawa, Real kq, Real yk,
+                                int bricked, int tab_r, int full_r, int far_ok, int yukawa, Real kq, Real yk,
                                 const YukawaLattice yl, double* __restrict__ out) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= count) return;
@@ -191,12 +191,13 @@ __global__ void lgf_eval_kernel(const int32_t* __restrict__ off, int64_t count, 
         return;
     }
     const int64_t lo = min(a, min(b, c)), hi = m, mid = a + b + c - lo - hi;
-    out[i] = (double)tab[hi * (hi + 1) * (hi + 2) / 6 + mid * (mid + 1) / 2 + lo];
+    if constexpr (sizeof(Real) == 8) out[i] = full_entry(tab, bricked != 0, (int)hi, (int)mid, (int)lo);
+    else out[i] = (double)tab[hi * (hi + 1) * (hi + 2) / 6 + mid * (mid + 1) / 2 + lo];
 }
 
 // Relative difference of the sigma > 0 far-field form (in FP64) and the table, over every
 // entry whose largest index lies in (from_r, R]; one maximum per block.
-__global__ void yukawa_check_kernel(const double* __restrict__ tab, int64_t e0, int64_t e1, double kq, double yk,
+__global__ void yukawa_check_kernel(const double* __restrict__ tab, int bricked, int64_t e0, int64_t e1, double kq, double yk,
                                     double* __restrict__ block_max) {
     __shared__ double sh[256];
     double worst = 0.0;
@@ -212,7 +213,8 @@ __global__ void yukawa_check_kernel(const double* __restrict__ tab, int64_t e0, 
         const int64_t a = rem - b * (b + 1) / 2;
         const double X = double(kQuant * a), Y = double(kQuant * b), Z = double(kQuant * c);
         const double f = far_field_yukawa<double>(X * X, Y * Y, Z * Z, kq, yk);
-        worst = fmax(worst, fabs(f - tab[e]) / fabs(tab[e]));
+        const double g = full_entry(tab, bricked != 0, (int)c, (int)b, (int)a);
+        worst = fmax(worst, fabs(f - g) / fabs(g));
     }
     sh[threadIdx.x] = worst;
     __syncthreads();
@@ -221,6 +223,15 @@ __global__ void yukawa_check_kernel(const double* __restrict__ tab, int64_t e0, 
         __syncthreads();
     }
     if (threadIdx.x == 0) block_max[blockIdx.x] = sh[0];
+}
+
+// A sorted table copied into bricks: block (mid, hi), one thread per lo.
+__global__ void table_bricks_kernel(const double* __restrict__ tab, double* __restrict__ out) {
+    const int hi = blockIdx.y, mid = blockIdx.x;
+    if (mid > hi) return;
+    const int64_t row = (int64_t)hi * (hi + 1) * (hi + 2) / 6 + (int64_t)mid * (mid + 1) / 2;
+    char* to = (char*)out + (brick_hi(hi) + brick_mid(mid));
+    for (int lo = threadIdx.x; lo <= mid; lo += blockDim.x) *(double*)(to + brick_lo(lo)) = tab[row + lo];
 }
 
 // ------------------------------------------------------------------ 16-RHS blocked form on MFMA
@@ -328,14 +339,14 @@ __device__ __forceinline__ void mfma_lookup_block(const SumArgs<Real>& a, const 
         uint32_t th[kTiles], tm[kTiles];
 #pragma unroll
         for (int j = 0; j < kTiles; ++j) {
-            th[j] = *(const uint32_t*)((const char*)L.tet + hi[j]);
-            tm[j] = *(const uint32_t*)((const char*)L.tri + mid[j]);
+            th[j] = index_hi<Real, GLOBAL>(L, hi[j]);
+            tm[j] = index_mid<Real, GLOBAL>(L, mid[j]);
         }
         __builtin_amdgcn_sched_barrier(0);
         wv = pw[4 * st];
 #pragma unroll
         for (int j = 0; j < kTiles; ++j) {
-            const uint32_t o = th[j] + tm[j] + (uint32_t)(sizeof(Real) / 4) * lo[j];
+            const uint32_t o = index_sum<Real, GLOBAL>(th[j], tm[j], lo[j]);
             g[j] = GLOBAL ? global_value(a.full_tab, o) : lds_value(L, o);
         }
     };
@@ -588,7 +599,7 @@ __global__ __launch_bounds__(THREADS) void lgf_sum_mfma_kernel(const SumArgs<Rea
     const Lds<Real> L = lds_layout<Real, FAR>(lds);
     __shared__ ItemRing ring;
     ring_init(&ring);
-    fill_lds(L, a.near_tab, a.tab_r, FAR ? a.tab_r : a.full_r);
+    fill_lds<Real, FAR>(L, a.near_tab, a.tab_r, FAR ? a.tab_r : a.full_r);
     __syncthreads();
     for_each_item(q, &ring, [&](uint32_t tile, uint32_t chunk) { mfma_tile<Real>(a, L, (int)tile, (int)chunk); });
 }
@@ -790,23 +801,28 @@ void lgf_eval_launch(const int32_t* off, int64_t count, double* out, int prec, c
     const unsigned blocks = (unsigned)((count + 255) / 256);
     const double kq = tabs.kappa / kQuant, yk = -tabs.kappa * 1.4426950408889634 / kQuant;
     if (prec == BAE_PREC_FP64)
-        lgf_eval_kernel<double><<<blocks, 256, 0, st>>>(off, count, tabs.full64, tabs.tab_r64, tabs.full_r,
-                                                        tabs.far64() ? 1 : 0, 0, kq, yk, YukawaLattice{}, out);
+        lgf_eval_kernel<double><<<blocks, 256, 0, st>>>(off, count, tabs.full64, tabs.bricked ? 1 : 0, tabs.tab_r64,
+                                                        tabs.full_r, tabs.far64() ? 1 : 0, 0, kq, yk, YukawaLattice{}, out);
     else
-        lgf_eval_kernel<float><<<blocks, 256, 0, st>>>(off, count, tabs.full32, tabs.tab_r32, tabs.full_r,
+        lgf_eval_kernel<float><<<blocks, 256, 0, st>>>(off, count, tabs.full32, 0, tabs.tab_r32, tabs.full_r,
                                                        tabs.far32() ? 1 : 0, tabs.yukawa32 ? 1 : 0, (float)kq,
                                                        (float)yk, yukawa_lattice(tabs.kappa), out);
     BAE_HIP_CHECK(hipGetLastError());
 }
 
-double yukawa_check(const double* table, int R, int from_r, double kappa, hipStream_t st) {
+void table_bricks(const double* table, int R, double* out, hipStream_t st) {
+    table_bricks_kernel<<<dim3((unsigned)R + 1, (unsigned)R + 1), 64, 0, st>>>(table, out);
+    BAE_HIP_CHECK(hipGetLastError());
+}
+
+double yukawa_check(const double* table, bool bricked, int R, int from_r, double kappa, hipStream_t st) {
     if (R <= from_r) return 0.0;
     const int64_t e0 = table_size(from_r), e1 = table_size(R);
     const int blocks = (int)std::min<int64_t>(1024, (e1 - e0 + 255) / 256);
     double* dmax = nullptr;
     BAE_HIP_CHECK(hipMalloc(&dmax, sizeof(double) * blocks));
-    yukawa_check_kernel<<<blocks, 256, 0, st>>>(table, e0, e1, kappa / kQuant, -kappa * 1.4426950408889634 / kQuant,
-                                                dmax);
+    yukawa_check_kernel<<<blocks, 256, 0, st>>>(table, bricked ? 1 : 0, e0, e1, kappa / kQuant,
+                                                -kappa * 1.4426950408889634 / kQuant, dmax);
     std::vector<double> h(blocks);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess) e = hipMemcpyAsync(h.data(), dmax, sizeof(double) * blocks, hipMemcpyDeviceToHost, st);
