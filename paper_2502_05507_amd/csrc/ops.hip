@@ -12,6 +12,12 @@ constexpr int kThreads = 256;
 
 inline unsigned blocks_for(int64_t n, int per = kThreads) { return (unsigned)((n + per - 1) / per); }
 
+// Loads in flight per thread of the chunk reduction and the dot products, added in their order (the last ones masked, not
+// one by one): these launches are chains of memory latencies.  In a 33^3 FP64 solve they took 5.6 and 4.5 us with a load
+// per turn, 4.2 and 3.5 so; the solve 2490 us and 2250, one operator call 25.2 and 22.0.  (The subtraction's loop the same way: 5.2 us against 4.1.)
+constexpr int kAhead = 16;
+constexpr int kDotAhead = 8;   // a slice is at most 2048 elements: one turn of kThreads
+
 // w[r][s] = sum_{j in row s} coef[j] q[r][col[j]]   (Sec. 3.2: w(n) = |D_n| q(n), w(k) = -sum q)
 // Rows in [ns, npad) are the padding sources of the last block: weight zero.
 template <typename Real>
@@ -43,7 +49,13 @@ __global__ __launch_bounds__(256) void reduce_chunks_kernel(const double* __rest
     double acc = 0.0;
     if (t < nt) {
         const double* p = part + r * ldp + t;
-        for (int c = cl; c < chunks; c += 4) acc += p[(int64_t)c * nt];
+        for (int c = cl; c < chunks; c += 4 * kAhead) {
+            double v[kAhead];
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) v[u] = p[(int64_t)min(c + 4 * u, chunks - 1) * nt];
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) acc = c + 4 * u < chunks ? acc + v[u] : acc;
+        }
     }
     sh[cl][tl] = acc;
     __syncthreads();
@@ -109,7 +121,17 @@ __global__ void dots_kernel(const double* __restrict__ X, int64_t ldx_vec, int64
     const double* x = X + r * ldx_rhs + j * ldx_vec;
     const double* yy = y + r * ldy;
     double acc = 0.0;
-    for (int64_t i = lo + threadIdx.x; i < hi; i += blockDim.x) acc = fma(x[i], yy[i], acc);
+    for (int64_t i = lo + threadIdx.x; i < hi; i += kDotAhead * kThreads) {
+        double xv[kDotAhead], yv[kDotAhead];
+#pragma unroll
+        for (int u = 0; u < kDotAhead; ++u) {
+            const int64_t at = min(i + u * kThreads, hi - 1);
+            xv[u] = x[at];
+            yv[u] = yy[at];
+        }
+#pragma unroll
+        for (int u = 0; u < kDotAhead; ++u) acc = i + u * kThreads < hi ? fma(xv[u], yv[u], acc) : acc;
+    }
     const double s = block_sum(acc, sh);
     if (threadIdx.x == 0) partial[((int64_t)r * maxj + j) * nb + b] = s;
 }
@@ -264,6 +286,8 @@ __device__ void givens_block(const GivensArgs& a, int r) {
         const double h1 = slice_sum(a.pA + ((int64_t)r * a.maxj + i) * a.nb, a.nb);
         return a.pB ? h1 + slice_sum(a.pB + ((int64_t)r * a.maxj + i) * a.nb, a.nb) : h1;
     };
+    double* gr = a.g + r * a.ldg;
+    const double gk = gr[k], beta = a.beta[r];   // before the chain, not behind it
     const double hk1_all = sqrt(block_slice_sum(a.npart + (int64_t)r * a.nn, a.nn));
     if (threadIdx.x == 0) {
         hk1s = hk1_all;
@@ -298,19 +322,19 @@ __device__ void givens_block(const GivensArgs& a, int r) {
     double* sw = a.sn + r * a.ldcs;
     const double x = carry, y = hk1;
     const double rr = hypot(x, y);
-    double* gr = a.g + r * a.ldg;
     if (rr == 0.0) {          // exact breakdown of a singular system: stop here
         a.done[r] = 1;
         a.kdone[r] = k;
         return;
     }
-    cw[k] = x / rr;
-    sw[k] = y / rr;
+    const double ck = x / rr, sk = y / rr, g1 = -sk * gk;
+    cw[k] = ck;
+    sw[k] = sk;
     h[k] = rr;
     h[k + 1] = 0.0;
-    gr[k + 1] = -sw[k] * gr[k];
-    gr[k] = cw[k] * gr[k];
-    const double est = fabs(gr[k + 1]) / a.beta[r];
+    gr[k + 1] = g1;
+    gr[k] = ck * gk;
+    const double est = fabs(g1) / beta;
     a.hist[r * a.ldhist + k] = est;
     a.kdone[r] = k + 1;
     if (est <= a.tol || hk1 == 0.0) a.done[r] = 1;
