@@ -14,7 +14,8 @@ inline unsigned blocks_for(int64_t n, int per = kThreads) { return (unsigned)((n
 
 // Loads in flight per thread of the chunk reduction and the dot products, added in their order (the last ones masked, not
 // one by one): these launches are chains of memory latencies.  In a 33^3 FP64 solve they took 5.6 and 4.5 us with a load
-// per turn, 4.2 and 3.5 so; the solve 2490 us and 2250, one operator call 25.2 and 22.0.  (The subtraction's loop the same way: 5.2 us against 4.1.)
+// per turn, 4.2 and 3.5 so; the solve 2490 us and 2250, one operator call 25.2 and 22.0.  (The subtraction's loop masked
+// the same way: 5.2 us against 4.1.)
 constexpr int kAhead = 16;
 constexpr int kDotAhead = 8;   // a slice is at most 2048 elements: one turn of kThreads
 
@@ -179,29 +180,40 @@ __global__ void dots_finalize_kernel(const double* __restrict__ partial, int nb,
 // y[r][i] -= sum_{j < nj} c[r][j] X[r][j][i], c[r][j] = the nb dot-product slices of
 // cpart summed by every block into LDS.  With npart, also the block's sum of the squared
 // results goes to npart[r][blockIdx.x] (slices of ||y[r]||^2).
-__global__ void subtract_combination_kernel(const double* __restrict__ X, int64_t ldx_vec, int64_t ldx_rhs,
-                                            const double* __restrict__ cpart, int nb, int maxj, int nj, int64_t n,
-                                            const int32_t* __restrict__ done, double* __restrict__ y,
-                                            int64_t ldy, double* __restrict__ npart) {
+// A block takes 64 rows, its wavefronts every fourth vector each: a quarter of the chain of loads, and four times the
+// blocks (256 rows to a block, one thread a row: 4.1 us on the 33^3 sphere, 3.7 so; 129^3 box solve 8.49 -> 8.13 ms).
+constexpr int kSubRows = 64;
+__global__ __launch_bounds__(kThreads) void subtract_combination_kernel(
+    const double* __restrict__ X, int64_t ldx_vec, int64_t ldx_rhs, const double* __restrict__ cpart, int nb, int maxj,
+    int nj, int64_t n, const int32_t* __restrict__ done, double* __restrict__ y, int64_t ldy, double* __restrict__ npart) {
+    constexpr int kW = kThreads / 64;
     extern __shared__ double cl[];   // nj coefficients
-    __shared__ double sh[kThreads / 64];
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    __shared__ double sh[kW][kSubRows];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t i = (int64_t)blockIdx.x * kSubRows + lane;
     const int r = blockIdx.y;
     if (done && done[r]) return;
     for (int j = threadIdx.x; j < nj; j += blockDim.x) cl[j] = slice_sum(cpart + ((int64_t)r * maxj + j) * nb, nb);
     __syncthreads();
-    double v2 = 0.0;
+    double acc = 0.0;
     if (i < n) {
         const double* x = X + r * ldx_rhs + i;
-        double acc = 0.0;
-        for (int j = 0; j < nj; ++j) acc = fma(cl[j], x[j * ldx_vec], acc);
+#pragma unroll 8
+        for (int j = wave; j < nj; j += kW) acc = fma(cl[j], x[j * ldx_vec], acc);
+    }
+    sh[wave][lane] = acc;
+    __syncthreads();
+    if (wave > 0) return;
+    double v2 = 0.0;
+    if (i < n) {
+        for (int k = 1; k < kW; ++k) acc += sh[k][lane];
         const double v = y[r * ldy + i] - acc;
         y[r * ldy + i] = v;
         v2 = v * v;
     }
     if (!npart) return;
-    const double s = block_sum(v2, sh);
-    if (threadIdx.x == 0) npart[(int64_t)r * gridDim.x + blockIdx.x] = s;
+    for (int o = 32; o > 0; o >>= 1) v2 += __shfl_down(v2, o, 64);
+    if (lane == 0) npart[(int64_t)r * gridDim.x + blockIdx.x] = v2;
 }
 
 // y[r][i] (+)= sum_{j < nj[r]} c[r][j] X[r][j][i]
@@ -527,12 +539,12 @@ void launch_subtract_combination(const double* X, int64_t ldx_vec, int64_t ldx_r
                                  int nj, int64_t n, int nrhs, const int32_t* done, double* y, int64_t ldy,
                                  double* npart, hipStream_t st) {
     const int nb = dot_blocks(n);
-    subtract_combination_kernel<<<dim3(blocks_for(n), nrhs), kThreads, sizeof(double) * nj, st>>>(
+    subtract_combination_kernel<<<dim3(blocks_for(n, kSubRows), nrhs), kThreads, sizeof(double) * nj, st>>>(
         X, ldx_vec, ldx_rhs, cpart, nb, maxj, nj, n, done, y, ldy, npart);
     LAUNCH_CHECK();
 }
 
-int norm_blocks(int64_t n) { return (int)blocks_for(n); }
+int norm_blocks(int64_t n) { return (int)blocks_for(n, kSubRows); }
 
 void launch_combination(const double* X, int64_t ldx_vec, int64_t ldx_rhs, const double* c, int64_t ldc,
                         const int32_t* nj, int64_t n, int nrhs, double* y, int64_t ldy, int accumulate,
