@@ -101,7 +101,7 @@ static void ensure_mplus(bae_ctx* c);
 
 // The FFT convolution of the LGF sum (lazy, once per context): its plan on the box of N+ u E
 // and the box index of every source and target.
-static void ensure_conv(bae_ctx* c, int nrhs, bool mplus = false) {
+static void ensure_conv(bae_ctx* c, int nrhs, hipStream_t st, bool mplus = false) {
     if (!c->conv) {
         const Geometry& G = c->geo;
         int64_t box = 1;
@@ -122,8 +122,8 @@ static void ensure_conv(bae_ctx* c, int nrhs, bool mplus = false) {
         mp->build(*c->conv, c->Mp.ps, c->stream);
         c->conv_mp = std::move(mp);
     }
-    c->conv->reserve(*c->conv_src, *c->conv_tgt, nrhs);
-    if (mplus) c->conv->reserve(*c->conv_mp, *c->conv_mp, nrhs);
+    c->conv->reserve(*c->conv_src, *c->conv_tgt, nrhs, st);
+    if (mplus) c->conv->reserve(*c->conv_mp, *c->conv_mp, nrhs, st);
 }
 
 // The current operator's LGF sum at the gamma targets (its sources, weights, work list), or
@@ -131,7 +131,7 @@ static void ensure_conv(bae_ctx* c, int nrhs, bool mplus = false) {
 static void apply_lgf(bae_ctx* c, const void* w, int nrhs, int prec, int* chunks_out, hipStream_t st,
                       const int32_t* skip = nullptr) {
     if (prec == BAE_PREC_FFT) {
-        ensure_conv(c, nrhs);
+        ensure_conv(c, nrhs, st);
         c->conv->apply((const double*)w, c->op.S->padded, c->op.direct ? *c->conv_tgt : *c->conv_src, *c->conv_tgt,
                        c->part.as<double>(), c->nT, nrhs, 1.0, skip, st);
         *chunks_out = 1;
@@ -1092,7 +1092,7 @@ static void set_rhs_impl(bae_ctx* c, int32_t nrhs, const double* g_xstar, const 
             if (!std::isfinite(f_grid[i])) throw Error{BAE_ERR_NONFINITE, "source term not finite"};
         ensure_lin(c);
         if (box) ensure_box(c);
-        else ensure_conv(c, nrhs, true);
+        else ensure_conv(c, nrhs, st, true);
         const int64_t nm = c->Mp.ps.count, nmp = c->Mp.ps.padded;
         std::vector<double> wfh(nmp * nrhs, 0.0);
         const double h2 = G.h * G.h;
@@ -1124,7 +1124,7 @@ static void set_rhs_device_impl(bae_ctx* c, int32_t nrhs, const double* g_dev, c
         // caller's work is touched
         ensure_lin(c);
         if (box) ensure_box(c);
-        else ensure_conv(c, nrhs, true);
+        else ensure_conv(c, nrhs, st, true);
         const int64_t nmp = c->Mp.ps.padded;
         if (c->wf.bytes < sizeof(double) * nmp * nrhs) c->wf.alloc(sizeof(double) * nmp * c->max_rhs);
         if (box && c->box_u.bytes < sizeof(double) * c->box_nn * nrhs)

@@ -772,16 +772,26 @@ void ConvPlan::build(const int lo_[3], const int hi_[3], const SumTables& tabs, 
     (void)hipFree(g);
 }
 
-void ConvPlan::reserve(const ConvPoints& src, const ConvPoints& tgt, int nrhs) {
+void ConvPlan::reserve(const ConvPoints& src, const ConvPoints& tgt, int nrhs, hipStream_t st) {
     const int64_t one = (int64_t)sizeof(double2) * e[0] * plane;
     const int want = (int)std::max<int64_t>(1, std::min<int64_t>(nrhs, kCacheBytes / one));
-    if (want > nc) {   // (the free waits for whatever still uses the smaller one)
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (want > nc && nc > 0) BAE_HIP_CHECK(hipStreamIsCapturing(st, &cap));
+    if (want > nc && cap == hipStreamCaptureStatusNone) {   // (the free waits for whatever still uses the smaller one;
+                                                            // under capture the groups stay as they are)
         BAE_HIP_CHECK(hipFree(C));
         C = nullptr;
         bytes -= one * nc;
         nc = 0;
-        device_alloc((void**)&C, one * want);
-        nc = want;
+        int got = want;
+        try {
+            device_alloc((void**)&C, one * got);
+        } catch (const Error&) {   // short of memory: one at a time, as before it grew
+            (void)hipGetLastError();
+            got = 1;
+            device_alloc((void**)&C, one);
+        }
+        nc = got;
         bytes += one * nc;
     }
     if (!R && !(src.sparse && tgt.sparse)) {
@@ -793,7 +803,7 @@ void ConvPlan::reserve(const ConvPoints& src, const ConvPoints& tgt, int nrhs) {
 
 void ConvPlan::apply(const double* w, int64_t ldw, const ConvPoints& src, const ConvPoints& tgt, double* out, int64_t ldo,
                      int nrhs, double scale, const int32_t* skip, hipStream_t st) {
-    reserve(src, tgt, nrhs);
+    reserve(src, tgt, nrhs, st);
     const int64_t box = (int64_t)e[0] * e[1] * e[2], one = (int64_t)e[0] * plane;
     const int64_t nrow = (int64_t)e[0] * e[1];
     const double norm = scale / ((double)M[0] * M[1] * M[2]);

@@ -49,7 +49,7 @@ struct ConvPlan {
     void build(const int lo_[3], const int hi_[3], const SumTables& tabs, hipStream_t st);
     // Allocates what apply needs for these sets and right-hand sides (no launches): C holds as many of them as
     // stay in the memory-side cache together.
-    void reserve(const ConvPoints& src, const ConvPoints& tgt, int nrhs);
+    void reserve(const ConvPoints& src, const ConvPoints& tgt, int nrhs, hipStream_t st);
     // out[r ldo + t] = scale sum_s w[r ldw + s] G(T_t - S_s) for r < nrhs; skipped while *skip is
     // set (when given).
     void apply(const double* w, int64_t ldw, const ConvPoints& src, const ConvPoints& tgt, double* out, int64_t ldo,
