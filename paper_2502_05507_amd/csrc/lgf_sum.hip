@@ -623,10 +623,11 @@ template <typename Real>
 constexpr int rhs4_threads() { return sizeof(Real) == 4 ? kSumThreads : kSumThreads / 2; }
 
 // Right-hand sides from which the matrix-core kernel takes a launch of up to 16 (its time does not depend on their
-// number), the 4-RHS kernel from two below it.  Times of 1 / 4 / 16 right-hand sides in us: FP64, sigma = 0, 93 / 143 /
-// 167 on the 65^3 ellipsoid and 1532 / 2041 / 2373 at 129^3; FP64, sigma > 0 (gathers), 82 / 152 / 121 and, on the 129^3
-// star, 2362 / 3915 / 3714, so that two already belong there; FP32 47 / 64 / 90, 486 / 706 / 939, star 1737 / 2625 / 2516.
-// (Launches of exactly 16, 4 and 1 took fifteen in six: 688 us where 176 do, FP64 at 65^3.)
+// number), the 4-RHS kernel from two below it.  Times of 1 / 4 / 16 right-hand sides in us: FP64, sigma = 0, 101 / 139 /
+// 150 on the 65^3 ellipsoid and 1435 / 2013 / 2052 at 129^3; FP64, sigma > 0 (gathers), 82 / 152 / 121 at 65^3 and
+// 2362 / 3915 / 3714 on the 129^3 star before its table went into bricks (117 and 3271 for 16 since), so that two already
+// belong there; FP32 47 / 63 / 85, 485 / 712 / 904, star 1734 / 2617 / 2466.
+// (Launches of exactly 16, 4 and 1 took fifteen in six: 688 us where 150 do, FP64 at 65^3.)
 template <typename Real>
 int mfma_from(bool far) { return sizeof(Real) == 8 && !far ? 2 : 5; }
 
