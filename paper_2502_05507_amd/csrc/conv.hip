@@ -248,8 +248,8 @@ __global__ __launch_bounds__(THREADS, THREADS == kLineThreads ? 3 : 2) void conv
         Stage<R, THREADS, false> s;
         constexpr int I = Stage<R, THREADS, false>::I;
         const Off gplane = (Off)H1 * (Off)K2;
-        auto kernel_value = [&](int pl, int n) {
-            return at_bytes(gbase, 8 * ((Off)min(n, M - n) * gplane + (Off)pl));
+        auto kernel_value = [&](int col, int n) {
+            return at_bytes(gbase, 8 * ((Off)min(n, M - n) * gplane + (Off)col));
         };
         // the values of the kernel's transform are in flight while the forward stage runs, where the registers
         // (168 of them) hold them beside its points
@@ -260,9 +260,9 @@ __global__ __launch_bounds__(THREADS, THREADS == kLineThreads ? 3 : 2) void conv
             for (int it = 0; it < I; ++it) {
                 const int e = threadIdx.x + it * THREADS;
                 if (e >= P * Ns) continue;
-                const int j = fdiv_up(e, L.rP), pl = e - j * P;
+                const int j = fdiv_up(e, L.rP), col = live_column(e - j * P, live);
 #pragma unroll
-                for (int k = 0; k < R; ++k) g[it][k] = kernel_value(pl, j + k * Ns);
+                for (int k = 0; k < R; ++k) g[it][k] = kernel_value(col, j + k * Ns);
             }
         }
         s.load(L, Ns, ld_lds);
@@ -270,9 +270,10 @@ __global__ __launch_bounds__(THREADS, THREADS == kLineThreads ? 3 : 2) void conv
 #pragma unroll
         for (int it = 0; it < I; ++it) {
             if (s.o[it] < 0) continue;
+            const int col = live_column(s.pl[it], live);
 #pragma unroll
             for (int k = 0; k < R; ++k)
-                s.v[it][k] = cscale(s.v[it][k], ahead ? g[it][k] : kernel_value(s.pl[it], s.o[it] + k * Ns));
+                s.v[it][k] = cscale(s.v[it][k], ahead ? g[it][k] : kernel_value(col, s.o[it] + k * Ns));
             dft<R, true>(s.v[it]);
             s.o[it] *= R;   // the inverse's first stage: outputs j R + k
         }
@@ -583,29 +584,6 @@ int split_rows(int M) {
 // The register-stage passes: kLineBlocks blocks to a compute unit, of four wavefronts at up to 168 VGPRs.
 constexpr int kLineBlocks = 3;
 bool short_lines(int M) { return M <= 8 * kLineThreads; }
-// Lines per block (the LDS holds their root table beside them): those for which the wavefronts' turns through the
-// stages, at about 9 + 14 R instructions each, are fewest per line.  A wavefront pays for a whole turn however
-// few of its lanes hold a butterfly: at M = 375 = 25 15, eight lines are 120 and 200 butterflies (2 and 4 wavefronts).
-int lines_for(const FftDev& p) {
-    const int threads = short_lines(p.M) ? kLineThreads : kLongThreads;
-    const size_t budget = short_lines(p.M) ? kFftLdsBytes / kLineBlocks : kFftLdsBytes;
-    const int most = std::min(kMaxLinesPerBlock, (int)((budget / sizeof(double2) - p.M) / (p.M | 1)));
-    int best = 1;
-    double best_cost = 1e300;
-    for (int P = 1; P <= most; ++P) {
-        double cost = 0.0;
-        for (int s = 0; s < p.nc; ++s) {
-            const int waves = (P * (p.M / p.c[s]) + 63) / 64;
-            if (P * (p.M / p.c[s]) > threads * fft_items(p.c[s], threads)) cost = 1e300;
-            cost += (double)waves * (9.0 + 14.0 * p.c[s]);
-        }
-        if (cost / P <= best_cost) {
-            best_cost = cost / P;
-            best = P;
-        }
-    }
-    return best;
-}
 size_t lines_lds(int M, int P, int roots) { return sizeof(double2) * ((size_t)P * (M | 1) + roots); }
 
 uint32_t mod_magic(int M) { return (uint32_t)((1ull << 32) / (uint64_t)M) + 1u; }
@@ -656,6 +634,30 @@ void device_alloc(void** p, size_t n) {
 }
 
 }  // namespace
+
+// Lines per block (the LDS holds their root table beside them): those for which the wavefronts' turns through the
+// stages, at about 9 + 14 R instructions each, are fewest per line.  A wavefront pays for a whole turn however
+// few of its lanes hold a butterfly: at M = 375 = 25 15, eight lines are 120 and 200 butterflies (2 and 4 wavefronts).
+int lines_for(const FftDev& p) {
+    const int threads = short_lines(p.M) ? kLineThreads : kLongThreads;
+    const size_t budget = short_lines(p.M) ? kFftLdsBytes / kLineBlocks : kFftLdsBytes;
+    const int most = std::min(kMaxLinesPerBlock, (int)((budget / sizeof(double2) - p.M) / (p.M | 1)));
+    int best = 1;
+    double best_cost = 1e300;
+    for (int P = 1; P <= most; ++P) {
+        double cost = 0.0;
+        for (int s = 0; s < p.nc; ++s) {
+            const int waves = (P * (p.M / p.c[s]) + 63) / 64;
+            if (P * (p.M / p.c[s]) > threads * fft_items(p.c[s], threads)) cost = 1e300;
+            cost += (double)waves * (9.0 + 14.0 * p.c[s]);
+        }
+        if (cost / P <= best_cost) {
+            best_cost = cost / P;
+            best = P;
+        }
+    }
+    return best;
+}
 
 int fft_smooth_length(int n) {
     for (int m = std::max(1, n);; ++m) {

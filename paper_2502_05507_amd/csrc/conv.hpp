@@ -56,6 +56,13 @@ struct ConvPlan {
                int nrhs, double scale, const int32_t* skip, hipStream_t st);
 };
 
+// Lines of a transform per block of the line passes (the LDS holds their root table beside them).
+int lines_for(const FftDev& p);
+
+// The column of the half spectrum that line pl of a block stands for, of its `live` columns: a block takes P lines
+// wherever it starts, and those past the last column must not read past the arrays' rows.
+__host__ __device__ inline int live_column(int pl, int live) { return pl < live ? pl : live - 1; }
+
 // Smallest length >= n whose prime factors are 2, 3 and 5 (the LDS FFT's register radices).
 int fft_smooth_length(int n);
 
