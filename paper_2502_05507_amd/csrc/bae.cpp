@@ -100,18 +100,19 @@ static int weight_prec(int prec) { return prec == BAE_PREC_FP32 ? BAE_PREC_FP32 
 static void ensure_mplus(bae_ctx* c);
 
 // The FFT convolution of the LGF sum (lazy, once per context): its plan on the box of N+ u E
-// and the box index of every source and target.
-static void ensure_conv(bae_ctx* c, int nrhs, hipStream_t st, bool mplus = false) {
+// and its sources and targets, all its memory with them (later calls only launch).
+static void ensure_conv(bae_ctx* c, bool mplus = false) {
     if (!c->conv) {
         const Geometry& G = c->geo;
         int64_t box = 1;
         for (int a = 0; a < 3; ++a) box *= (int64_t)(G.bbox_hi[a] - G.bbox_lo[a] + 1);
         if (box > INT32_MAX) throw Error{BAE_ERR_ARG, "LGF convolution: box beyond 2^31 nodes"};
         auto cp = std::make_unique<ConvPlan>();
-        cp->build(G.bbox_lo, G.bbox_hi, c->tabs, c->stream);
+        cp->build(G.bbox_lo, G.bbox_hi, c->tabs, c->max_rhs, c->stream);
         auto src = std::make_unique<ConvPoints>(), tgt = std::make_unique<ConvPoints>();
         src->build(*cp, c->S.ps, c->stream);
         tgt->build(*cp, c->T.ps, c->stream);
+        if (!src->sparse || !tgt->sparse) cp->dense_rows();
         c->conv_src = std::move(src);
         c->conv_tgt = std::move(tgt);
         c->conv = std::move(cp);
@@ -120,10 +121,9 @@ static void ensure_conv(bae_ctx* c, int nrhs, hipStream_t st, bool mplus = false
         ensure_mplus(c);
         auto mp = std::make_unique<ConvPoints>();
         mp->build(*c->conv, c->Mp.ps, c->stream);
+        if (!mp->sparse) c->conv->dense_rows();
         c->conv_mp = std::move(mp);
     }
-    c->conv->reserve(*c->conv_src, *c->conv_tgt, nrhs, st);
-    if (mplus) c->conv->reserve(*c->conv_mp, *c->conv_mp, nrhs, st);
 }
 
 // The current operator's LGF sum at the gamma targets (its sources, weights, work list), or
@@ -131,7 +131,7 @@ static void ensure_conv(bae_ctx* c, int nrhs, hipStream_t st, bool mplus = false
 static void apply_lgf(bae_ctx* c, const void* w, int nrhs, int prec, int* chunks_out, hipStream_t st,
                       const int32_t* skip = nullptr) {
     if (prec == BAE_PREC_FFT) {
-        ensure_conv(c, nrhs, st);
+        ensure_conv(c);
         c->conv->apply((const double*)w, c->op.S->padded, c->op.direct ? *c->conv_tgt : *c->conv_src, *c->conv_tgt,
                        c->part.as<double>(), c->nT, nrhs, 1.0, skip, st);
         *chunks_out = 1;
@@ -1092,7 +1092,7 @@ static void set_rhs_impl(bae_ctx* c, int32_t nrhs, const double* g_xstar, const 
             if (!std::isfinite(f_grid[i])) throw Error{BAE_ERR_NONFINITE, "source term not finite"};
         ensure_lin(c);
         if (box) ensure_box(c);
-        else ensure_conv(c, nrhs, st, true);
+        else ensure_conv(c, true);
         const int64_t nm = c->Mp.ps.count, nmp = c->Mp.ps.padded;
         std::vector<double> wfh(nmp * nrhs, 0.0);
         const double h2 = G.h * G.h;
@@ -1124,7 +1124,7 @@ static void set_rhs_device_impl(bae_ctx* c, int32_t nrhs, const double* g_dev, c
         // caller's work is touched
         ensure_lin(c);
         if (box) ensure_box(c);
-        else ensure_conv(c, nrhs, st, true);
+        else ensure_conv(c, true);
         const int64_t nmp = c->Mp.ps.padded;
         if (c->wf.bytes < sizeof(double) * nmp * nrhs) c->wf.alloc(sizeof(double) * nmp * c->max_rhs);
         if (box && c->box_u.bytes < sizeof(double) * c->box_nn * nrhs)

@@ -628,6 +628,7 @@ constexpr int64_t kCacheBytes = 128ll << 20;
 
 void device_alloc(void** p, size_t n) {
     if (hipMalloc(p, n) != hipSuccess) {
+        (void)hipGetLastError();
         *p = nullptr;
         throw Error{BAE_ERR_OOM, "LGF convolution: device allocation failed"};
     }
@@ -729,7 +730,7 @@ ConvPlan::~ConvPlan() {
     (void)hipFree(C);
 }
 
-void ConvPlan::build(const int lo_[3], const int hi_[3], const SumTables& tabs, hipStream_t st) {
+void ConvPlan::build(const int lo_[3], const int hi_[3], const SumTables& tabs, int max_rhs, hipStream_t st) {
     for (int a = 0; a < 3; ++a) {
         lo[a] = lo_[a];
         e[a] = hi_[a] - lo_[a] + 1;
@@ -749,12 +750,22 @@ void ConvPlan::build(const int lo_[3], const int hi_[3], const SumTables& tabs, 
     plane = (int64_t)M[1] * K2;
     const int64_t one = (int64_t)sizeof(double2) * e[0] * plane;
     device_alloc((void**)&ghat, sizeof(double) * oct);
-    device_alloc((void**)&C, one);
-    nc = 1;
-    bytes = sizeof(double) * oct + one;
-    // the kernel's transform: sample, three full passes (z, y, x), keep one octant
+    nc = (int)std::max<int64_t>(1, std::min<int64_t>(max_rhs, kCacheBytes / one));
+    // the kernel's transform: sample, three full passes (z, y, x), keep one octant.  Its grid takes C's memory where
+    // that is no larger than a group's may be: an allocation and its release are 0.3 ms each, the kernels 0.06 at
+    // 65^3 and 0.15 at 129^3 (a first apply there 0.9 and 1.1 ms with a grid of its own, 0.24 and 0.6 so).
+    const int64_t grid = (int64_t)sizeof(double2) * full;
+    int64_t held = 0;   // bytes of C
     double2* g = nullptr;
-    device_alloc((void**)&g, sizeof(double2) * full);
+    if (grid <= kCacheBytes) {
+        try {
+            device_alloc((void**)&C, std::max(one * nc, grid));
+            held = std::max(one * nc, grid);
+            g = C;
+        } catch (const Error&) {   // short of memory: in turn, below
+        }
+    }
+    if (!C) device_alloc((void**)&g, grid);
     try {
         conv_kernel_grid<<<(unsigned)((full + 255) / 256), 256, 0, st>>>(g, M[0], M[1], M[2], e[0], e[1], e[2],
                                                                           tabs.full64, tabs.bricked ? 1 : 0, tabs.tab_r64,
@@ -768,44 +779,33 @@ void ConvPlan::build(const int lo_[3], const int hi_[3], const SumTables& tabs, 
         BAE_HIP_CHECK(hipStreamSynchronize(st));
     } catch (...) {
         (void)hipStreamSynchronize(st);
-        (void)hipFree(g);
+        if (!C) (void)hipFree(g);
         throw;
     }
-    (void)hipFree(g);
-}
-
-void ConvPlan::reserve(const ConvPoints& src, const ConvPoints& tgt, int nrhs, hipStream_t st) {
-    const int64_t one = (int64_t)sizeof(double2) * e[0] * plane;
-    const int want = (int)std::max<int64_t>(1, std::min<int64_t>(nrhs, kCacheBytes / one));
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (want > nc && nc > 0) BAE_HIP_CHECK(hipStreamIsCapturing(st, &cap));
-    if (want > nc && cap == hipStreamCaptureStatusNone) {   // (the free waits for whatever still uses the smaller one;
-                                                            // under capture the groups stay as they are)
-        BAE_HIP_CHECK(hipFree(C));
-        C = nullptr;
-        bytes -= one * nc;
-        nc = 0;
-        int got = want;
+    if (!C) {
+        (void)hipFree(g);
         try {
-            device_alloc((void**)&C, one * got);
-        } catch (const Error&) {   // short of memory: one at a time, as before it grew
-            (void)hipGetLastError();
-            got = 1;
+            device_alloc((void**)&C, one * nc);
+        } catch (const Error&) {   // short of memory
+            if (nc == 1) throw;
+            nc = 1;
             device_alloc((void**)&C, one);
         }
-        nc = got;
-        bytes += one * nc;
+        held = one * nc;
     }
-    if (!R && !(src.sparse && tgt.sparse)) {
-        const int64_t box = (int64_t)e[0] * e[1] * e[2];
-        device_alloc((void**)&R, sizeof(double) * box);
-        bytes += sizeof(double) * box;
-    }
+    bytes = (int64_t)sizeof(double) * oct + held;
+}
+
+void ConvPlan::dense_rows() {
+    if (R) return;
+    const int64_t box = (int64_t)e[0] * e[1] * e[2];
+    device_alloc((void**)&R, sizeof(double) * box);
+    bytes += sizeof(double) * box;
 }
 
 void ConvPlan::apply(const double* w, int64_t ldw, const ConvPoints& src, const ConvPoints& tgt, double* out, int64_t ldo,
                      int nrhs, double scale, const int32_t* skip, hipStream_t st) {
-    reserve(src, tgt, nrhs, st);
+    if (!R && !(src.sparse && tgt.sparse)) throw Error{BAE_ERR_STATE, "LGF convolution: no dense rows"};
     const int64_t box = (int64_t)e[0] * e[1] * e[2], one = (int64_t)e[0] * plane;
     const int64_t nrow = (int64_t)e[0] * e[1];
     const double norm = scale / ((double)M[0] * M[1] * M[2]);

@@ -41,17 +41,18 @@ struct ConvPlan {
     double* ghat = nullptr;       // [H0][H1][K2] real: the kernel's transform on one octant
     double* R = nullptr;          // [e0][e1][e2] real: a dense set's weights in, potentials out (lazy)
     double2* C = nullptr;         // [nc][e0][M1][K2] complex: the partly transformed grids of nc right-hand sides
-    int nc = 0;                   // grows to the right-hand sides asked for
+    int nc = 0;                   // right-hand sides of a group
     int64_t bytes = 0;
     ~ConvPlan();
     // Plans, the kernel's transform (G exactly as the FP64 sum evaluates it: the table within
-    // tab_r64, the far-field expansion beyond it when the sum has one, else the full table).
-    void build(const int lo_[3], const int hi_[3], const SumTables& tabs, hipStream_t st);
-    // Allocates what apply needs for these sets and right-hand sides (no launches): C holds as many of them as
-    // stay in the memory-side cache together.
-    void reserve(const ConvPoints& src, const ConvPoints& tgt, int nrhs, hipStream_t st);
-    // out[r ldo + t] = scale sum_s w[r ldw + s] G(T_t - S_s) for r < nrhs; skipped while *skip is
-    // set (when given).
+    // tab_r64, the far-field expansion beyond it when the sum has one, else the full table), and C for as many of
+    // max_rhs right-hand sides as stay in the memory-side cache together (one where memory is short).  C stays where
+    // it is until the plan ends: a graph captured from an apply holds its address.
+    void build(const int lo_[3], const int hi_[3], const SumTables& tabs, int max_rhs, hipStream_t st);
+    // Allocates R once, before a set that is not sparse is first used.
+    void dense_rows();
+    // out[r ldo + t] = scale sum_s w[r ldw + s] G(T_t - S_s) for any nrhs (r < nrhs), in groups of nc; skipped while
+    // *skip is set (when given).  Launches only.
     void apply(const double* w, int64_t ldw, const ConvPoints& src, const ConvPoints& tgt, double* out, int64_t ldo,
                int nrhs, double scale, const int32_t* skip, hipStream_t st);
 };
