@@ -628,7 +628,6 @@ void build_layout(BatchEngine* b) {
             a.nblk = (int)c->S.ps.nblk;
             a.blk_per_chunk = b->blk_per_chunk;
             a.ldw = c->S.ps.padded;
-            a.nr = 1;
             a.near_tab = near;
             a.full_tab = full;
             a.full_r = c->tabs.full_r;

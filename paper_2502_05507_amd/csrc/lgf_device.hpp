@@ -448,7 +448,7 @@ struct SumArgs {
     int ns, nblk, blk_per_chunk;
     const Real* w;
     int64_t ldw;
-    int nr;                           // right-hand sides of the launch (a kernel's further ones repeat the last, unstored)
+    int nr = 1;                       // right-hand sides of a matrix-core launch (its further rows repeat the last, unstored)
     const Real* near_tab;             // table prefix staged in LDS (radius tab_r)
     const Real* full_tab;             // full table (sigma > 0): radius full_r; FP64: in bricks
     int tab_r;                        // LDS table radius used (<= the kernel's tab_radius)
@@ -509,7 +509,7 @@ __device__ __forceinline__ Step<Real, NR, U> load_step(const SumArgs<Real>& a, i
         st.zr = ldu_vec<Real, U>(a.szr, s0);
     }
 #pragma unroll
-    for (int r = 0; r < NR; ++r) st.w[r] = ldu_vec<Real, U>(a.w, (NR > 1 ? min(r, a.nr - 1) : 0) * a.ldw + s0);
+    for (int r = 0; r < NR; ++r) st.w[r] = ldu_vec<Real, U>(a.w, r * a.ldw + s0);
     __builtin_amdgcn_sched_barrier(0);
     return st;
 }
@@ -701,8 +701,7 @@ __device__ __forceinline__ void sum_tile(const SumArgs<Real>& a, const Lds<Real>
     }
     if (t < a.nt) {
 #pragma unroll
-        for (int r = 0; r < NR; ++r)
-            if (NR == 1 || r < a.nr) a.part[(int64_t)r * a.ldp + (int64_t)chunk * a.nt + t] = acc[r].value();
+        for (int r = 0; r < NR; ++r) a.part[(int64_t)r * a.ldp + (int64_t)chunk * a.nt + t] = acc[r].value();
     }
 }
 

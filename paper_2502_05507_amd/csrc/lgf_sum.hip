@@ -13,8 +13,8 @@
 //   c >  RL : sigma = 0 -> far-field expansion in registers (valid beyond 32, below; q = 4
 //             in FP64, q = 2 in FP32, where the FP32 rounding of the sum dominates);
 //             sigma > 0 -> the full FP64/FP32 table in global memory (L2 / MALL resident)
-// A table lookup costs 8 VALU instructions per pair, the FP32 far field 15 and the FP64 one
-// 37, so every block pair that fits the LDS table is evaluated from it.
+// A table lookup costs 8 VALU instructions per pair (FP64 9), the FP32 far field 15 and the FP64
+// one 33 (one of them the rsq estimate), so every block pair that fits the LDS table is evaluated from it.
 // Far field (sigma = 0): Sec. 2.2 q-term expansion in the positive sign convention,
 //   G_0(n) = (1/(4 pi |n|)) [1 + rho (1 - 5x)/4 + rho^2 P8/32 + rho^3 P12/128] + O(|n|^-9),
 //   rho = 1/|n|^2, x = e2 rho^2, y = e3 rho^3, e2 = j^2k^2 + k^2l^2 + l^2j^2, e3 = j^2k^2l^2,
@@ -40,6 +40,7 @@
 #include <algorithm>
 #include <map>
 #include <mutex>
+#include <type_traits>
 
 #include "lgf_device.hpp"
 #include "ops.hpp"
@@ -615,21 +616,27 @@ const double* coord<double>(const PointSet& P, int axis) {
     return axis == 0 ? P.xd : axis == 1 ? P.yd : P.zd;
 }
 
-// Workgroup sizes: 16 wavefronts, except the FP64 4-RHS and matrix-core kernels, whose
+// Workgroup sizes: 16 wavefronts, except the FP64 kernels of several right-hand sides, whose
 // accumulators need the registers of 8.
 template <typename Real>
 constexpr int mfma_threads() { return sizeof(Real) == 4 ? kSumThreads : kSumThreads / 2; }
 template <typename Real>
-constexpr int rhs4_threads() { return sizeof(Real) == 4 ? kSumThreads : kSumThreads / 2; }
+constexpr int valu_threads(int nr) { return sizeof(Real) == 4 || nr == 1 ? kSumThreads : kSumThreads / 2; }
 
-// Right-hand sides from which the matrix-core kernel takes a launch of up to 16 (its time does not depend on their
-// number), the 4-RHS kernel from two below it.  Times of 1 / 4 / 16 right-hand sides in us: FP64, sigma = 0, 101 / 139 /
-// 150 on the 65^3 ellipsoid and 1435 / 2013 / 2052 at 129^3; FP64, sigma > 0 (gathers), 82 / 152 / 121 at 65^3 and
-// 2362 / 3915 / 3714 on the 129^3 star before its table went into bricks (117 and 3271 for 16 since), so that two already
-// belong there; FP32 47 / 63 / 85, 485 / 712 / 904, star 1734 / 2617 / 2466.
-// (Launches of exactly 16, 4 and 1 took fifteen in six: 688 us where 150 do, FP64 at 65^3.)
+// Right-hand sides from which the matrix-core kernel takes a launch of up to 16 (its time hardly depends on their
+// number); below it the VALU kernel of exactly that number.  One double layer of 1 / 2 / 3 / 4 right-hand sides by the
+// VALU kernels and of 5 and 16 (*: 2 and 16) by the matrix-core kernel, in us:
+//   FP64, sigma = 0   65^3 ellipsoid 96 / 119 / 127 / 143, 151 and 161; 129^3 1315 / 1685 / 1777 / 1952, 2030 and 2080
+//   FP64, sigma > 0   49^3 (table in LDS) 33, 46* and 59; 65^3 85, 112* and 132; 129^3 star 2040, 2810* and 3330
+//                     (the VALU kernel of four, on the sorted table: 55, 175 and 4050; two launches of one: 61, 160, 4550)
+//   FP32, sigma = 0   65^3 50 / 56 / 62 / 70, 86 and 98; 129^3 497 / 567 / 627 / 703, 863 and 932
+//   FP32, sigma > 0   65^3 50 / 56 / 62 / 70, 85 and 98; 129^3 star 1746 / 1950 / 2456 / 2615, 2370 and 2465
+// (three and four on a far-dominated FP32 sum at sigma > 0 would gain 4 and 9% by the matrix-core kernel and lose 37 and
+// 22% on a table-dominated one).  A VALU kernel of four for two to four, its further rows repeating the last, took
+// 707 / 716 / 725 in FP32 at 129^3 and 2000 / 2004 / 2030 in FP64; launches of 16, 4 and 1 took fifteen in six: 712 us
+// where 161 do, FP64 at 65^3.
 template <typename Real>
-int mfma_from(bool far) { return sizeof(Real) == 8 && !far ? 2 : 5; }
+constexpr int mfma_from(bool far) { return sizeof(Real) == 8 && !far ? 2 : 5; }
 
 template <typename Real>
 void launch_all(const PointSet& T, const PointSet& S, const Real* w, int nrhs, const Real* near, const Real* full,
@@ -680,14 +687,18 @@ void launch_all(const PointSet& T, const PointSet& S, const Real* w, int nrhs, c
             ar.nr = std::min(left, 16);
             if (lds_far) lgf_sum_mfma_kernel<Real, mfma_threads<Real>(), true><<<grid, mfma_threads<Real>(), 0, st>>>(ar, q);
             else lgf_sum_mfma_kernel<Real, mfma_threads<Real>(), false><<<grid, mfma_threads<Real>(), 0, st>>>(ar, q);
-        } else if (left >= 2) {
-            ar.nr = std::min(left, 4);
-            if (lds_far) lgf_sum_kernel<Real, 4, rhs4_threads<Real>(), true><<<grid, rhs4_threads<Real>(), 0, st>>>(ar, q);
-            else lgf_sum_kernel<Real, 4, rhs4_threads<Real>(), false><<<grid, rhs4_threads<Real>(), 0, st>>>(ar, q);
         } else {
-            ar.nr = 1;
-            if (lds_far) lgf_sum_kernel<Real, 1, kSumThreads, true><<<grid, kSumThreads, 0, st>>>(ar, q);
-            else lgf_sum_kernel<Real, 1, kSumThreads, false><<<grid, kSumThreads, 0, st>>>(ar, q);
+            ar.nr = left;
+            auto valu = [&](auto n) {
+                constexpr int NR = decltype(n)::value, threads = valu_threads<Real>(NR);
+                if (lds_far) lgf_sum_kernel<Real, NR, threads, true><<<grid, threads, 0, st>>>(ar, q);
+                else if constexpr (NR < mfma_from<Real>(false))
+                    lgf_sum_kernel<Real, NR, threads, false><<<grid, threads, 0, st>>>(ar, q);
+            };
+            if (left == 1) valu(std::integral_constant<int, 1>{});
+            else if (left == 2) valu(std::integral_constant<int, 2>{});
+            else if (left == 3) valu(std::integral_constant<int, 3>{});
+            else valu(std::integral_constant<int, 4>{});
         }
         r += ar.nr;
         BAE_HIP_CHECK(hipGetLastError());
