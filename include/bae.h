@@ -361,8 +361,8 @@ int bae_batch_create(bae_ctx* const* ctxs, int32_t n, bae_batch** out);
  * Time the LGF-sum tiling candidates (source blocks per chunk in {2, 4, 8, 16, 32, 64} x
  * persistent grid of {1, 2, 4} workgroups per compute unit) on this batch at `precision`,
  * keep the fastest, and append it to the tuning cache
- * ($BAE_AUTOTUNE_CACHE, else ~/.cache/bae_autotune.txt; keyed by GPU arch, log2 of the
- * pair count and of the batch size) that bae_batch_create reads.  chosen: 2 int32 (or NULL).
+ * ($BAE_AUTOTUNE_CACHE, else ~/.cache/bae_autotune.txt; keyed by GPU arch and
+ * scheduler, log2 of the pair count and of the batch size) that bae_batch_create reads.  chosen: 2 int32 (or NULL).
  */
 int bae_batch_autotune(bae_batch* b, int32_t precision, int32_t* chosen);
 /*

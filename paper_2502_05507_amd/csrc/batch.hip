@@ -885,8 +885,10 @@ std::string tune_key(BatchEngine* b) {
     double pairs = 0;
     for (auto* c : b->ctx) pairs += (double)c->nT * c->nS;
     std::ostringstream k;
-    k << prop.gcnArchName << " " << (int)std::lround(std::log2(std::max(pairs, 1.0))) << " "
-      << (int)std::lround(std::log2((double)std::max(b->np, 1)));
+    // "/drawn": tilings tuned for items in a fixed round-robin (16 blocks per chunk, say) are not the fastest for drawn
+    // ones (24 problems of 32 to 64 nodes per axis, FP64: 27.8 ms with 16, 25.0 with 8), and their lines not read
+    k << prop.gcnArchName << "/drawn " << (int)std::lround(std::log2(std::max(pairs, 1.0))) << " "
+      << (int)std::lround(std::log2((double)b->ctx.size()));   // (np is set with the layout, later)
     return k.str();
 }
 
