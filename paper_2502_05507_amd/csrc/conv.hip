@@ -116,13 +116,6 @@ __device__ __forceinline__ T& at_bytes(T* base, Off off) {
     return *(T*)((char*)base + off);
 }
 
-// a mod M for a < 2^23, M <= kFftMaxLen (magic = floor(2^32 / M) + 1): the quotient by the high product is exact
-// or one too large, and the unsigned minimum takes back the step where it is.
-__device__ __forceinline__ uint32_t mod_by(uint32_t a, uint32_t M, uint32_t magic) {
-    const uint32_t t = a - __umulhi(a, magic) * M;
-    return min(t, t + M);
-}
-
 // Forward transforms along y: the lines k of plane i (element n at n K2 + k) hold the z spectra at k of the plane's
 // rows n of range[i] (all n < e1 without it), zero beyond.  A block takes P lines k of one plane.
 // What bounds it: writing C (318 MB per right-hand side at 257^3): 95 us, 4.8 TB/s (143 us before the register stages).
@@ -585,8 +578,6 @@ int split_rows(int M) {
 constexpr int kLineBlocks = 3;
 bool short_lines(int M) { return M <= 8 * kLineThreads; }
 size_t lines_lds(int M, int P, int roots) { return sizeof(double2) * ((size_t)P * (M | 1) + roots); }
-
-uint32_t mod_magic(int M) { return (uint32_t)((1ull << 32) / (uint64_t)M) + 1u; }
 
 void set_lds_attr() {
     static std::once_flag once;   // (per process: the attribute holds for every device of one architecture)

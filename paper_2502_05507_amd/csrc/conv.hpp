@@ -64,6 +64,14 @@ int lines_for(const FftDev& p);
 // wherever it starts, and those past the last column must not read past the arrays' rows.
 __host__ __device__ inline int live_column(int pl, int live) { return pl < live ? pl : live - 1; }
 
+// a mod M for a < 2^23, 2 <= M <= kFftMaxLen, with mod_magic(M) = floor(2^32 / M) + 1: the quotient by the high product
+// is exact or one too large, and the unsigned minimum takes back the step where it is.
+inline uint32_t mod_magic(int M) { return (uint32_t)((1ull << 32) / (uint64_t)M) + 1u; }
+__host__ __device__ inline uint32_t mod_by(uint32_t a, uint32_t M, uint32_t magic) {
+    const uint32_t t = a - (uint32_t)(((uint64_t)a * magic) >> 32) * M;
+    return t < t + M ? t : t + M;
+}
+
 // Smallest length >= n whose prime factors are 2, 3 and 5 (the LDS FFT's register radices).
 int fft_smooth_length(int n);
 

@@ -61,6 +61,8 @@ __host__ __device__ constexpr uint32_t brick_mid(int mid) {
     return 128u * ((uint32_t)((mid / 2 + 1) * (mid / 2 + 1)) / 4u) + 32u * (mid & 1);
 }
 __host__ __device__ constexpr uint32_t brick_lo(int lo) { return 128u * (uint32_t)(lo / 4) + 8u * (lo & 3); }
+// brick_lo(q / kQuant) from the quantised q
+__host__ __device__ constexpr uint32_t brick_lo_quantised(uint32_t q) { return 2u * q + 96u * (q >> 4); }
 __host__ __device__ constexpr int64_t brick_entries(int R) { return 16 * brick_count(R / 2 + 1); }   // radius R
 // FP64 table G_s for 0<=a<=b<=c<=R into out (device), on stream.
 void lgf_table_generate(double s, int R, double* out, hipStream_t stream);

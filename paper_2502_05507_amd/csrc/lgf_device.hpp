@@ -339,7 +339,7 @@ __device__ __forceinline__ uint32_t index_mid(const Lds<Real>& L, uint32_t mid) 
 template <typename Real, bool GLOBAL>
 __device__ __forceinline__ uint32_t index_sum(uint32_t th, uint32_t tm, uint32_t lo) {   // lo quantised
     if constexpr (sizeof(Real) == 4) return th + tm + lo;
-    else if constexpr (GLOBAL) return th + tm + 2u * lo + 96u * (lo >> 4);   // brick_lo(lo / kQuant)
+    else if constexpr (GLOBAL) return th + tm + brick_lo_quantised(lo);
     else return th + tm + 2u * lo;
 }
 template <typename Real>
