@@ -64,3 +64,26 @@ def test_volume_potential(axis):
             want.append(p.h ** 2 * float(G.cpu().numpy() @ f[tuple(inner.T)]))
     # positive terms: the transforms' rounding, some 1e-15 of the largest value on the box, which is a few times these
     assert rel_l2(got[rows], np.array(want)) < 1e-12
+
+
+def test_x_pass_beyond_4_gb():
+    """Two balls in opposite corners of a box whose x pass takes 64-bit offsets: its smallest radix, 3 of 2187, spans
+    more than 4 GB of the grid."""
+    import torch
+    n, r = (1095, 243, 771), 2.6
+    phi = np.full(n, 1.0)
+    for at in ([6, 6, 6], [m - 7 for m in n]):
+        near = np.ogrid[tuple(slice(a - 4, a + 5) for a in at)]
+        phi[tuple(slice(a - 4, a + 5) for a in at)] = np.sqrt(sum((x - a) ** 2 for x, a in zip(near, at))) - r
+    with P.Context(n, 1.0 / 64, (0.0, 0.0, 0.0), 0.0, "sampled", phi=phi, max_rhs=2, max_krylov=8) as c:
+        del phi
+        q = torch.from_numpy(np.random.default_rng(5).standard_normal((2, c.sizes["n_gamma_minus"]))).to(device())
+        a, b = (torch.empty((2, c.sizes["n_targets"]), dtype=torch.float64, device=device()) for _ in range(2))
+        c.apply_double_layer(q, a, P.PREC_FFT)
+        c.apply_double_layer(q, b, P.PREC_FP64)
+        torch.cuda.synchronize()
+        M = c.get_sizes()["conv_fft"]
+        assert M[0] == 2187 and (M[0] // 3 + 1) * M[1] * (M[2] // 2 + 1) * 16 > 2 ** 32
+    for r in range(2):
+        # the direct sum is exact to its far field's 7e-11 (the FFT takes the same kernel values)
+        assert rel_l2(a[r].cpu().numpy(), b[r].cpu().numpy()) < 1e-10
