@@ -30,7 +30,6 @@ namespace {
 using namespace fftdev;
 
 constexpr int kConvThreads = kFftThreads;
-constexpr int kMaxLinesPerBlock = 32;   // lines_for's cap (packed real rows included)
 constexpr int kIt = kFftPoints / kConvThreads;   // elements per thread of a block's lines, at most
 
 __device__ __forceinline__ int64_t idx3(int i, int j, int k, int n1, int n2) { return ((int64_t)i * n1 + j) * n2 + k; }
@@ -241,8 +240,10 @@ __global__ __launch_bounds__(THREADS, THREADS == kLineThreads ? 3 : 2) void conv
         Stage<R, THREADS, false> s;
         constexpr int I = Stage<R, THREADS, false>::I;
         const Off gplane = (Off)H1 * (Off)K2;
-        auto kernel_value = [&](int col, int n) {
-            return at_bytes(gbase, 8 * ((Off)min(n, M - n) * gplane + (Off)col));
+        // (of lines past the row's columns too: octant_entries has room for them, and they are not stored.  Clamped to
+        // the last column, whose registers this pass lacks, 16 right-hand sides at 257^3 took 10.2 ms, 9.6 so)
+        auto kernel_value = [&](int pl, int n) {
+            return at_bytes(gbase, 8 * ((Off)min(n, M - n) * gplane + (Off)pl));
         };
         // the values of the kernel's transform are in flight while the forward stage runs, where the registers
         // (168 of them) hold them beside its points
@@ -253,9 +254,9 @@ __global__ __launch_bounds__(THREADS, THREADS == kLineThreads ? 3 : 2) void conv
             for (int it = 0; it < I; ++it) {
                 const int e = threadIdx.x + it * THREADS;
                 if (e >= P * Ns) continue;
-                const int j = fdiv_up(e, L.rP), col = live_column(e - j * P, live);
+                const int j = fdiv_up(e, L.rP), pl = e - j * P;
 #pragma unroll
-                for (int k = 0; k < R; ++k) g[it][k] = kernel_value(col, j + k * Ns);
+                for (int k = 0; k < R; ++k) g[it][k] = kernel_value(pl, j + k * Ns);
             }
         }
         s.load(L, Ns, ld_lds);
@@ -263,10 +264,9 @@ __global__ __launch_bounds__(THREADS, THREADS == kLineThreads ? 3 : 2) void conv
 #pragma unroll
         for (int it = 0; it < I; ++it) {
             if (s.o[it] < 0) continue;
-            const int col = live_column(s.pl[it], live);
 #pragma unroll
             for (int k = 0; k < R; ++k)
-                s.v[it][k] = cscale(s.v[it][k], ahead ? g[it][k] : kernel_value(col, s.o[it] + k * Ns));
+                s.v[it][k] = cscale(s.v[it][k], ahead ? g[it][k] : kernel_value(s.pl[it], s.o[it] + k * Ns));
             dft<R, true>(s.v[it]);
             s.o[it] *= R;   // the inverse's first stage: outputs j R + k
         }
@@ -527,13 +527,13 @@ __global__ void conv_kernel_grid(double2* __restrict__ g, int M0, int M1, int M2
     g[q] = make_double2(v, 0.0);
 }
 
-// The real part of the transformed kernel on the octant [H0][H1][H2] (rows K2 apart).
+// The real part of the transformed kernel on the octant [H0][H1][H2] (rows K2 apart), zeros elsewhere.
 __global__ void conv_octant(const double2* __restrict__ g, int M1, int M2, int H0, int H1, int H2, int K2,
                             double* __restrict__ out) {
     const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= (int64_t)H0 * H1 * K2) return;
+    if (q >= octant_entries(H0, H1, K2)) return;
     const int a = (int)(q / ((int64_t)H1 * K2)), b = (int)((q / K2) % H1), c = (int)(q % K2);
-    out[q] = c < H2 ? g[idx3(a, b, c, M1, M2)].x : 0.0;
+    out[q] = a < H0 && c < H2 ? g[idx3(a, b, c, M1, M2)].x : 0.0;
 }
 
 __global__ void conv_scatter(const double* __restrict__ w, const int32_t* __restrict__ sidx, int64_t ns,
@@ -737,7 +737,7 @@ void ConvPlan::build(const int lo_[3], const int hi_[3], const SumTables& tabs, 
     fy = fft_plan(M[1], st);
     fz = fft_plan(M[2], st);
     if (!fx.nc || !fy.nc || !fz.nc) throw Error{BAE_ERR_ARG, "LGF convolution: a length without register radices"};
-    const int64_t full = (int64_t)M[0] * M[1] * M[2], oct = (int64_t)H[0] * H[1] * K2;
+    const int64_t full = (int64_t)M[0] * M[1] * M[2], oct = octant_entries(H[0], H[1], K2);
     plane = (int64_t)M[1] * K2;
     const int64_t one = (int64_t)sizeof(double2) * e[0] * plane;
     device_alloc((void**)&ghat, sizeof(double) * oct);

@@ -38,7 +38,7 @@ struct ConvPlan {
     int K2 = 0;                   // pitch of the half spectra along z: H2 rounded up to 128 bytes of C
     int64_t plane = 0;            // pitch of the planes of C
     FftDev fx, fy, fz;            // transforms along the three axes (lengths M0, M1, M2)
-    double* ghat = nullptr;       // [H0][H1][K2] real: the kernel's transform on one octant
+    double* ghat = nullptr;       // [H0][H1][K2] real (octant_entries): the kernel's transform on one octant
     double* R = nullptr;          // [e0][e1][e2] real: a dense set's weights in, potentials out (lazy)
     double2* C = nullptr;         // [nc][e0][M1][K2] complex: the partly transformed grids of nc right-hand sides
     int nc = 0;                   // right-hand sides of a group
@@ -60,9 +60,12 @@ struct ConvPlan {
 // Lines of a transform per block of the line passes (the LDS holds their root table beside them).
 int lines_for(const FftDev& p);
 
-// The column of the half spectrum that line pl of a block stands for, of its `live` columns: a block takes P lines
-// wherever it starts, and those past the last column must not read past the arrays' rows.
-__host__ __device__ inline int live_column(int pl, int live) { return pl < live ? pl : live - 1; }
+constexpr int kMaxLinesPerBlock = 32;   // lines_for's cap (packed real rows included)
+// Values of the kernel's transform on the octant [H0][H1][H2], rows K2 apart: a block of the x pass takes P lines
+// wherever it starts and reads the values of them all, up to P - 1 past the end of its row.
+__host__ __device__ constexpr int64_t octant_entries(int H0, int H1, int K2) {
+    return (int64_t)H0 * H1 * K2 + kMaxLinesPerBlock;
+}
 
 // a mod M for a < 2^23, 2 <= M <= kFftMaxLen, with mod_magic(M) = floor(2^32 / M) + 1: the quotient by the high product
 // is exact or one too large, and the unsigned minimum takes back the step where it is.
