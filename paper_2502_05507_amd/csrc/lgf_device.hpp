@@ -21,7 +21,7 @@ constexpr int kWave = 64;
 template <typename Real>
 constexpr int unroll() { return 4; }   // sources per unrolled step
 // Sources per step of the one-RHS table loop: 32-byte scalar loads, twice as many LDS reads in
-// flight.  Every other loop takes 4, so that its double-buffered sources leave the block loop
+// flight.  Every other loop (but the one-RHS FP64 far one, at its place) takes 4, so that its double-buffered sources leave the block loop
 // enough scalar registers (with 8 everywhere the FP32 sum spilled 69 of them to VGPR lanes and
 // restored them in every block; far-dominated sums ran 7% slower).
 template <typename Real, int NR>
@@ -134,7 +134,8 @@ __device__ __forceinline__ void far_pairs4v(const uint32_t (&t)[4], uint32_t s, 
 
 // FP64: q = 4 from the quantised offset components (not all 0); relative error <= 6.6e-11
 // beyond the far-field gap.  The arithmetic bounds the FP64 sums, so it is written for its
-// instruction count (31 and the estimate; 129^3 ellipsoid 1403 us with 34, 1324 so): with z = Z/r^2 and w = X Y/r^4, the symmetric
+// instruction count (28 and the estimate here, 33 in all with the offsets and the accumulation;
+// 129^3 ellipsoid 1403 us with three more, 1324 so): with z = Z/r^2 and w = X Y/r^4, the symmetric
 // functions e2/r^4 and e3/r^6 of the squares are z (1 - z) + w and z w; and the Newton step of
 // the inverse square root, y (3 - r^2 y^2)/2 (relative error about 1.5 e0^2 for an estimate error
 // e0, no special cases to handle), shares y^2 and its bracket with 1/r^2 and leaves its half

@@ -181,7 +181,7 @@ __global__ void dots_finalize_kernel(const double* __restrict__ partial, int nb,
 // cpart summed by every block into LDS.  With npart, also the block's sum of the squared
 // results goes to npart[r][blockIdx.x] (slices of ||y[r]||^2).
 // A block takes 64 rows, its wavefronts every fourth vector each: a quarter of the chain of loads, and four times the
-// blocks (256 rows to a block, one thread a row: 4.1 us on the 33^3 sphere, 3.7 so; 129^3 box solve 8.49 -> 8.13 ms).
+// blocks (256 rows to a block, one thread a row: 4.1 us on the 33^3 sphere, 3.7 so; 129^3 box solve 8.49 -> 8.29 ms).
 constexpr int kSubRows = 64;
 __global__ __launch_bounds__(kThreads) void subtract_combination_kernel(
     const double* __restrict__ X, int64_t ldx_vec, int64_t ldx_rhs, const double* __restrict__ cpart, int nb, int maxj,
