@@ -15,8 +15,8 @@ inline unsigned blocks_for(int64_t n, int per = kThreads) { return (unsigned)((n
 // Loads in flight per thread of the chunk reduction and the dot products, added in their order (the last ones masked, not
 // one by one): these launches are chains of memory latencies.  In a 33^3 FP64 solve they took 5.6 and 4.5 us with a load
 // per turn, 4.2 and 3.5 so; the solve 2490 us and 2250, one operator call 25.2 and 22.0.  (The subtraction's loop masked
-// the same way: 5.2 us against 4.1.)
-constexpr int kAhead = 16;
+// the same way: 5.2 us against 4.1.)  The reduction's kAhead: as many as a lane's chunks fill (one chunk, as the FFT
+// convolution leaves, of 16 right-hand sides on 229848 targets: 40 us with 16 loads, 29 with one).
 constexpr int kDotAhead = 8;   // a slice is at most 2048 elements: one turn of kThreads
 
 // w[r][s] = sum_{j in row s} coef[j] q[r][col[j]]   (Sec. 3.2: w(n) = |D_n| q(n), w(k) = -sum q)
@@ -40,6 +40,7 @@ __global__ void weights_kernel(const int32_t* __restrict__ rowptr, const int32_t
 // out[r][pos(t)] = scale * sum over chunks of part[r][c][t].  A block covers 64 targets
 // with 4 chunk lanes (chunk c goes to lane c mod 4; every load is a coalesced 512-byte row),
 // the lane sums combined in a fixed order, so results do not vary between runs.
+template <int kAhead>
 __global__ __launch_bounds__(256) void reduce_chunks_kernel(const double* __restrict__ part, int chunks, int64_t nt,
                                                             int64_t ldp, const int32_t* __restrict__ pos,
                                                             double* __restrict__ out, int64_t ldo, double scale) {
@@ -493,7 +494,13 @@ void launch_reduce_scatter(const double* part, int chunks, int64_t nt, const int
                            int nrhs, double scale, hipStream_t st) {
     if (nt == 0) return;
     dim3 grid((unsigned)((nt + 63) / 64), nrhs);
-    reduce_chunks_kernel<<<grid, 256, 0, st>>>(part, chunks, nt, (int64_t)chunks * nt, pos, out, ldo, scale);
+    auto run = [&](auto ahead) {
+        reduce_chunks_kernel<decltype(ahead)::value>
+            <<<grid, 256, 0, st>>>(part, chunks, nt, (int64_t)chunks * nt, pos, out, ldo, scale);
+    };
+    if (chunks <= 4) run(std::integral_constant<int, 1>{});
+    else if (chunks <= 16) run(std::integral_constant<int, 4>{});
+    else run(std::integral_constant<int, 16>{});
     LAUNCH_CHECK();
 }
 
