@@ -261,7 +261,7 @@ static void ensure_direct(bae_ctx* c) {
         for (DevMem* d : {&c->x, &c->r, &c->tmp}) d->alloc(sizeof(double) * n * mr);
         c->kV.alloc(sizeof(double) * (m + 1) * n * mr);
         c->K.V = c->kV.as<double>();
-        c->dotpart.alloc(sizeof(double) * mr * (2 * (int64_t)c->maxj * dot_blocks(n) + norm_blocks(n)));
+        c->dotpart.alloc(sizeof(double) * (mr * 2 * (int64_t)c->maxj * dot_blocks(n) + norm_slots(n, mr)));
         c->vec_cap = n;
     }
     BAE_HIP_CHECK(hipStreamSynchronize(st));
@@ -771,7 +771,7 @@ bae_ctx* create_context(const bae_grid& gridv, const bae_options* opt, Geometry&
         c->hA.alloc(sizeof(double) * c->maxj * mr);
         c->hB.alloc(sizeof(double) * c->maxj * mr);
         c->nrm.alloc(sizeof(double) * c->maxj * mr);
-        c->dotpart.alloc(sizeof(double) * mr * (2 * (int64_t)c->maxj * dot_blocks(n) + norm_blocks(n)));
+        c->dotpart.alloc(sizeof(double) * (mr * 2 * (int64_t)c->maxj * dot_blocks(n) + norm_slots(n, mr)));
         c->ycoef.alloc(sizeof(double) * m * mr);
         for (DevMem* d : {&c->b, &c->x, &c->r, &c->tmp}) d->alloc(sizeof(double) * n * mr);
         c->up_gamma.alloc(sizeof(double) * c->nT * mr);
@@ -846,7 +846,7 @@ int64_t estimate_context_bytes(const Geometry& G, double s, const bae_options* o
     b += nT * mr * 8;                                                                     // reduced sums
     b += ((int64_t)(m + 1) * ngm + (int64_t)m * (m + 1) + 4 * m + 8) * 8 * mr;        // Krylov state
     b += (int64_t)(m + 1) * mr * 8 * (3 + 2 * dot_blocks(ngm)) + (int64_t)m * mr * 8;  // CGS, dot slices, y
-    b += (int64_t)norm_blocks(ngm) * mr * 8;                                           // norm slices
+    b += norm_slots(ngm, mr) * 8;                                                      // norm slices
     b += 4 * ngm * mr * 8 + 2 * nT * mr * 8;                                           // b, x, r, tmp, u_p, u_gamma
     const int64_t pr = std::min<int64_t>(kRecycleDefault, m);
     b += (2 * ngm + (int64_t)m * dot_blocks(ngm)) * pr * mr * 8;                      // refined solves' recycling

@@ -181,17 +181,23 @@ __global__ void dots_finalize_kernel(const double* __restrict__ partial, int nb,
 // y[r][i] -= sum_{j < nj} c[r][j] X[r][j][i], c[r][j] = the nb dot-product slices of
 // cpart summed by every block into LDS.  With npart, also the block's sum of the squared
 // results goes to npart[r][blockIdx.x] (slices of ||y[r]||^2).
-// A block takes 64 rows, its wavefronts every fourth vector each: a quarter of the chain of loads, and four times the
-// blocks (256 rows to a block, one thread a row: 4.1 us on the 33^3 sphere, 3.7 so; 129^3 box solve 8.49 -> 8.29 ms).
+// A block takes ROWS rows, kThreads / ROWS threads to a row, which share the vectors.  With 64 rows the chain of
+// loads is a quarter as long and there are four times the blocks (33^3 sphere 4.1 -> 3.7 us; 129^3 box solve 8.49 ->
+// 8.29 ms); but each sums all the coefficients, and whoever takes the norm four times the slices.  sub_rows: 64 while
+// blocks of 256 would not give every compute unit one.  64 / 256 rows, us per launch: 65182 x 1 right-hand sides
+// 6.9 / 7.2, 19346 x 4 7.1 / 7.0, 115646 x 1 10.9 / 10.1, 19346 x 16 19 / 16, 115646 x 16 145 / 97, where the closing
+// launch takes 77 / 55.
 constexpr int kSubRows = 64;
+int sub_rows(int64_t n, int nrhs) { return (int64_t)blocks_for(n) * nrhs <= 256 ? kSubRows : kThreads; }
+template <int ROWS>
 __global__ __launch_bounds__(kThreads) void subtract_combination_kernel(
     const double* __restrict__ X, int64_t ldx_vec, int64_t ldx_rhs, const double* __restrict__ cpart, int nb, int maxj,
     int nj, int64_t n, const int32_t* __restrict__ done, double* __restrict__ y, int64_t ldy, double* __restrict__ npart) {
-    constexpr int kW = kThreads / 64;
+    constexpr int kW = kThreads / ROWS;
     extern __shared__ double cl[];   // nj coefficients
-    __shared__ double sh[kW][kSubRows];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t i = (int64_t)blockIdx.x * kSubRows + lane;
+    __shared__ double sh[kThreads];
+    const int lane = threadIdx.x % ROWS, part = threadIdx.x / ROWS;
+    const int64_t i = (int64_t)blockIdx.x * ROWS + lane;
     const int r = blockIdx.y;
     if (done && done[r]) return;
     for (int j = threadIdx.x; j < nj; j += blockDim.x) cl[j] = slice_sum(cpart + ((int64_t)r * maxj + j) * nb, nb);
@@ -199,22 +205,32 @@ __global__ __launch_bounds__(kThreads) void subtract_combination_kernel(
     double acc = 0.0;
     if (i < n) {
         const double* x = X + r * ldx_rhs + i;
+        if constexpr (kW > 1) {
 #pragma unroll 8
-        for (int j = wave; j < nj; j += kW) acc = fma(cl[j], x[j * ldx_vec], acc);
+            for (int j = part; j < nj; j += kW) acc = fma(cl[j], x[j * ldx_vec], acc);
+        } else {
+            for (int j = 0; j < nj; ++j) acc = fma(cl[j], x[j * ldx_vec], acc);
+        }
     }
-    sh[wave][lane] = acc;
-    __syncthreads();
-    if (wave > 0) return;
+    if constexpr (kW > 1) {
+        sh[threadIdx.x] = acc;
+        __syncthreads();
+        if (part > 0) return;
+        for (int k = 1; k < kW; ++k) acc += sh[k * ROWS + lane];
+    }
     double v2 = 0.0;
     if (i < n) {
-        for (int k = 1; k < kW; ++k) acc += sh[k][lane];
         const double v = y[r * ldy + i] - acc;
         y[r * ldy + i] = v;
         v2 = v * v;
     }
     if (!npart) return;
-    for (int o = 32; o > 0; o >>= 1) v2 += __shfl_down(v2, o, 64);
-    if (lane == 0) npart[(int64_t)r * gridDim.x + blockIdx.x] = v2;
+    if constexpr (kW > 1) {
+        for (int o = 32; o > 0; o >>= 1) v2 += __shfl_down(v2, o, 64);
+    } else {
+        v2 = block_sum(v2, sh);
+    }
+    if (threadIdx.x == 0) npart[(int64_t)r * gridDim.x + blockIdx.x] = v2;
 }
 
 // y[r][i] (+)= sum_{j < nj[r]} c[r][j] X[r][j][i]
@@ -546,12 +562,23 @@ void launch_subtract_combination(const double* X, int64_t ldx_vec, int64_t ldx_r
                                  int nj, int64_t n, int nrhs, const int32_t* done, double* y, int64_t ldy,
                                  double* npart, hipStream_t st) {
     const int nb = dot_blocks(n);
-    subtract_combination_kernel<<<dim3(blocks_for(n, kSubRows), nrhs), kThreads, sizeof(double) * nj, st>>>(
-        X, ldx_vec, ldx_rhs, cpart, nb, maxj, nj, n, done, y, ldy, npart);
+    const dim3 grid(norm_blocks(n, nrhs), nrhs);
+    const size_t lds = sizeof(double) * nj;
+    if (sub_rows(n, nrhs) == kSubRows)
+        subtract_combination_kernel<kSubRows><<<grid, kThreads, lds, st>>>(X, ldx_vec, ldx_rhs, cpart, nb, maxj, nj, n, done,
+                                                                           y, ldy, npart);
+    else
+        subtract_combination_kernel<kThreads><<<grid, kThreads, lds, st>>>(X, ldx_vec, ldx_rhs, cpart, nb, maxj, nj, n, done,
+                                                                           y, ldy, npart);
     LAUNCH_CHECK();
 }
 
-int norm_blocks(int64_t n) { return (int)blocks_for(n, kSubRows); }
+int norm_blocks(int64_t n, int nrhs) { return (int)blocks_for(n, sub_rows(n, nrhs)); }
+int64_t norm_slots(int64_t n, int max_rhs) {
+    int64_t most = 0;
+    for (int r = 1; r <= max_rhs; ++r) most = std::max<int64_t>(most, (int64_t)norm_blocks(n, r) * r);
+    return most;
+}
 
 void launch_combination(const double* X, int64_t ldx_vec, int64_t ldx_rhs, const double* c, int64_t ldc,
                         const int32_t* nj, int64_t n, int nrhs, double* y, int64_t ldy, int accumulate,
@@ -564,19 +591,19 @@ void launch_combination(const double* X, int64_t ldx_vec, int64_t ldx_rhs, const
 void launch_normalize(double* V, int64_t ldv_vec, int64_t ldv_rhs, int k, int64_t n, const double* npart,
                       const int32_t* done, int nrhs, hipStream_t st) {
     normalize_kernel<<<dim3(blocks_for(n), nrhs), kThreads, 0, st>>>(V, ldv_vec, ldv_rhs, k, n, npart,
-                                                                      norm_blocks(n), done);
+                                                                      norm_blocks(n, nrhs), done);
     LAUNCH_CHECK();
 }
 
 static GivensArgs givens_args(const KrylovState& K, const double* pA, const double* pB, int maxj, const double* npart,
-                              int k, double tol) {
-    return GivensArgs{K.H, K.m + 1, (int64_t)(K.m + 1) * K.m, pA, pB, dot_blocks(K.n), maxj, npart, norm_blocks(K.n),
+                              int k, double tol, int nrhs) {
+    return GivensArgs{K.H, K.m + 1, (int64_t)(K.m + 1) * K.m, pA, pB, dot_blocks(K.n), maxj, npart, norm_blocks(K.n, nrhs),
                       K.cs, K.sn, K.m, K.g, K.m + 1, K.beta, K.hist, K.m, K.done, K.kdone, k, tol};
 }
 
 void launch_givens(const KrylovState& K, const double* pA, const double* pB, int maxj, const double* npart, int k,
                    double tol, int nrhs, hipStream_t st) {
-    givens_kernel<<<nrhs, kThreads, 0, st>>>(givens_args(K, pA, pB, maxj, npart, k, tol));
+    givens_kernel<<<nrhs, kThreads, 0, st>>>(givens_args(K, pA, pB, maxj, npart, k, tol, nrhs));
     LAUNCH_CHECK();
 }
 
@@ -585,7 +612,7 @@ void launch_finish(const KrylovState& K, const double* wv, int64_t ldwv, const d
                    int32_t* host_flag, hipStream_t st) {
     const int nbn = (int)blocks_for(K.n), nbw = (int)blocks_for(B.padded_rows);
     const dim3 grid(nbn + nbw + 1, nrhs);
-    const GivensArgs ga = givens_args(K, pA, pB, maxj, npart, k, tol);
+    const GivensArgs ga = givens_args(K, pA, pB, maxj, npart, k, tol, nrhs);
     if (prec == BAE_PREC_FP64)
         finish_kernel<double><<<grid, kThreads, 0, st>>>(K.V, K.n, K.ld_rhs, wv, ldwv, K.n, nbn, nbw, B.rowptr, B.col,
                                                           B.coef, B.rows, B.padded_rows, (double*)w, ldw, ga,

@@ -62,11 +62,13 @@ void launch_dots(const double* X, int64_t ldx_vec, int64_t ldx_rhs, int nj, cons
 void launch_dot_slices(const double* X, int64_t ldx_vec, int64_t ldx_rhs, int nj, const double* y, int64_t ldy,
                        int64_t n, int nrhs, const int32_t* done, double* partial, int maxj, hipStream_t st);
 // y[r] -= sum_j c[r][j] X[r][j] with c the summed slices of cpart; with npart non-null also
-// the slices of ||y[r]||^2 (npart[r][b], b < norm_blocks(n)).
+// the slices of ||y[r]||^2 (npart[r][b], b < norm_blocks(n, nrhs)).
 void launch_subtract_combination(const double* X, int64_t ldx_vec, int64_t ldx_rhs, const double* cpart, int maxj,
                                  int nj, int64_t n, int nrhs, const int32_t* done, double* y, int64_t ldy,
                                  double* npart, hipStream_t st);
-int norm_blocks(int64_t n);
+int norm_blocks(int64_t n, int nrhs);
+// The most of them, over all right-hand sides, for up to max_rhs.
+int64_t norm_slots(int64_t n, int max_rhs);
 // out[r][l] = sum_{j < kin} X[r][j] M[r][j][l], l < kout; M [nrhs][kin][kout] on the device.
 void launch_basis_transform(const double* X, int64_t ldx_vec, int64_t ldx_rhs, int kin, const double* M, int kout,
                             int64_t n, int nrhs, double* out, int64_t ldo_vec, int64_t ldo_rhs, hipStream_t st);
