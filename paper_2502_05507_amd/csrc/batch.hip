@@ -100,24 +100,34 @@ __global__ void b_weights(const BProb* __restrict__ P, const int64_t* __restrict
 // Persistent LGF sum over (problem, 1024-target tile, source chunk) items: each of the 16
 // wavefronts of a workgroup takes one 64-target tile of the item.  The LDS table is
 // restaged only when an item needs another table (sigma > 0 problems each have their own;
-// every sigma = 0 problem shares one) or a larger prefix of it.  A workgroup's first item is its own index, each
-// further one comes from a counter (drawn while the item before is evaluated): items differ in cost (tables, partly
-// filled tiles, converged problems), and in a fixed round-robin the last workgroups set the time (352 us per sum of 24
-// problems of 32 to 64 nodes per axis; drawn 297).
+// every sigma = 0 problem shares one) or a larger prefix of it.
+// Items differ in cost (tables, partly filled tiles, converged problems).  A workgroup takes its first fixed_turns items in
+// a fixed round-robin and the rest from a counter (draw_plan): the first wavefront, which has a tile in every item, draws
+// one ahead, while the item before is evaluated, into a slot of LDS that the others read.  They wait for each other
+// to restage a table and after the items that draw_plan says; those without a tile run one turn ahead at most.
+constexpr int kSlots = 64;   // the slots of half of them are free again at every kSlots / 2 turns' barrier
 template <typename Real>
 __global__ __launch_bounds__(kSumThreads) void b_lgf_sum(const BProb* __restrict__ P, const Item* __restrict__ items,
-                                                         int nitems, int use_done, const int32_t* __restrict__ sel,
+                                                         int nitems, int fixed_turns, int in_step,
+                                                         int use_done, const int32_t* __restrict__ sel,
                                                          int32_t* __restrict__ next_item) {
     __shared__ __align__(16) char lds[lds_bytes<Real, false>()];
-    __shared__ int32_t drawn[2];
+    __shared__ int32_t slots[kSlots];   // by turn: the item, or kFree
+    constexpr int32_t kFree = -1;
     const Lds<Real> L = lds_layout<Real, false>(lds);
     fill_index<Real, false>(L, kMaxR);
+    if (threadIdx.x < kSlots) slots[threadIdx.x] = kFree;
+    __syncthreads();
     const Real* cur = nullptr;
     int cur_r = -1;
     const int wave = threadIdx.x >> 6;
     int it = blockIdx.x;
-    for (int turn = 0; it < nitems; ++turn) {
-        if (threadIdx.x == 0) drawn[turn & 1] = (int32_t)gridDim.x + atomicAdd(next_item, 1);
+    for (int turn = 0; it < nitems; ++turn) {   // every wavefront sees the same items
+        const bool drawn = turn + 1 >= fixed_turns;
+        int32_t* const slot = &slots[(turn + 1) % kSlots];
+        if (drawn && threadIdx.x == 0)
+            __hip_atomic_store(slot, fixed_turns * (int32_t)gridDim.x + atomicAdd(next_item, 1), __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_WORKGROUP);
         const Item w = items[it];
         const BProb& q = P[w.p];
         if (!((use_done && q.done[0]) || (sel && !sel[w.p]))) {   // uniform over the block
@@ -133,9 +143,20 @@ __global__ __launch_bounds__(kSumThreads) void b_lgf_sum(const BProb* __restrict
             // every problem here is small: its chunk fits the scalar cache only while the
             // item's wavefronts walk it together, so no rotation
             if (tile * kWave < a.nt) sum_tile<Real, 1, false>(a, L, tile, w.chunk);
+            if (in_step || (sizeof(Real) == 8 && a.far_ok)) __syncthreads();
         }
-        __syncthreads();
-        it = drawn[turn & 1];   // (the slot is written again two turns on, past the next barrier)
+        if (drawn) {   // (the first wavefront stores before it waits for anything in its turn)
+            int32_t got;
+            while ((got = __hip_atomic_load(slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) < 0)
+                __builtin_amdgcn_s_sleep(1);
+            it = __builtin_amdgcn_readfirstlane(got);
+            if ((turn + 1) % (kSlots / 2) == 0) {   // all have read the slots of the turns up to this one
+                __syncthreads();
+                if (threadIdx.x < kSlots / 2) slots[(turn + 1 - threadIdx.x + kSlots) % kSlots] = kFree;
+            }
+        } else {
+            it += gridDim.x;
+        }
     }
 }
 
@@ -665,6 +686,26 @@ void build_layout(BatchEngine* b) {
     BAE_HIP_CHECK(hipStreamSynchronize(st));
 }
 
+// How the workgroups take the items: fixed_turns of b_lgf_sum, and in_step, after which items its wavefronts wait for each
+// other: all, or (FP64) those of sigma = 0.  By the items to a workgroup, 16 iterations in ms, all in a fixed round-robin /
+// all drawn and in step / as here, FP64 and FP32:
+//   8 problems of 48 to 64 nodes per axis (4)   6.73 / 7.32 / 7.32    4.49 / 4.60 / 4.60
+//   24 of 32 to 64 (11)                         14.5 / 12.5 / 12.5    10.7 / 10.4 / 10.4
+//   one of 129 (11)                             29.5 / 28.8 / 28.9    14.0 / 14.8 / 14.2
+//   6 of 81 to 91 (18)                          34.4 / 33.3 / 33.4    21.1 / 19.9 / 19.2
+//   161, 129, 113 and 97 (60)                   125 / 126 / 121       77.2 / 83.4 / 73.7
+//   64 of 32 to 96 (88)                         137 / 132 / 128       85.5 / 85.8 / 81.3
+// (one of 225, 64 FP64 iterations: 968 drawn in step, 1030 out of step, 970 here.)  Drawing evens out the end: the last 16
+// turns; before them converged problems' items are passed over without a draw.  In step, the wavefronts share a chunk's
+// sources in the scalar cache, which FP64's 22 KB need more than FP32's 14 KB, but wait for the slowest of each item.
+struct DrawPlan {
+    int fixed_turns, in_step;
+};
+DrawPlan draw_plan(int nitems, unsigned grid, bool fp64) {
+    const int turns = nitems / (int)grid;
+    return DrawPlan{std::max(1, turns - 16), turns <= (fp64 ? 20 : 4)};
+}
+
 // one operator application for all (or all unfinished) problems, src 0: V[k], 1: x;
 // dst 0: V[k+1], 1: tmp, -1: partial sums only
 void apply_all(BatchEngine* b, int prec, int src, int dst, int use_done, const int32_t* sel = nullptr) {
@@ -672,14 +713,20 @@ void apply_all(BatchEngine* b, int prec, int src, int dst, int use_done, const i
     const BProb* P = b->probs.as<BProb>();
     const unsigned grid = (unsigned)std::max(1, std::min(b->nitems, b->grid_mult * b->n_cu));
     int32_t* next = b->next_item.as<int32_t>();
+    auto sum = [&](auto real) {
+        using Real = decltype(real);
+        const DrawPlan plan = draw_plan(b->nitems, grid, sizeof(Real) == 8);
+        b_lgf_sum<Real><<<grid, kSumThreads, 0, st>>>(P, b->items.as<Item>(), b->nitems, plan.fixed_turns, plan.in_step,
+                                                      use_done, sel, next);
+    };
     if (prec == BAE_PREC_FP64) {
         b_weights<double><<<nblocks(b->tot_src), kT, 0, st>>>(P, b->off_src.as<int64_t>(), b->np, b->tot_src, src,
                                                               use_done, sel, next);
-        b_lgf_sum<double><<<grid, kSumThreads, 0, st>>>(P, b->items.as<Item>(), b->nitems, use_done, sel, next);
+        sum(double{});
     } else {
         b_weights<float><<<nblocks(b->tot_src), kT, 0, st>>>(P, b->off_src.as<int64_t>(), b->np, b->tot_src, src,
                                                              use_done, sel, next);
-        b_lgf_sum<float><<<grid, kSumThreads, 0, st>>>(P, b->items.as<Item>(), b->nitems, use_done, sel, next);
+        sum(float{});
     }
     if (dst >= 0)
         b_closure<<<nblocks(b->tot_row), kT, 0, st>>>(P, b->off_row.as<int64_t>(), b->np, b->tot_row, dst, use_done,
