@@ -695,15 +695,17 @@ void build_layout(BatchEngine* b) {
 //   6 of 81 to 91 (18)                          34.4 / 33.3 / 33.4    21.1 / 19.9 / 19.2
 //   161, 129, 113 and 97 (60)                   125 / 126 / 121       77.2 / 83.4 / 73.7
 //   64 of 32 to 96 (88)                         137 / 132 / 128       85.5 / 85.8 / 81.3
-// (one of 225, 64 FP64 iterations: 968 drawn in step, 1030 out of step, 970 here.)  Drawing evens out the end: the last 16
-// turns; before them converged problems' items are passed over without a draw.  In step, the wavefronts share a chunk's
-// sources in the scalar cache, which FP64's 22 KB need more than FP32's 14 KB, but wait for the slowest of each item.
+// (one of 225, 64 FP64 iterations: 968 drawn in step, 1030 out of step, 970 here.)  Drawing evens out the end, and what
+// converged problems leave: the last 32 turns; before them such problems' items are passed over without a draw (512
+// problems of 32 to 96 to 1e-10, 64 blocks per chunk: 840 ms all drawn, 845 so, 875 with the last 16).  In step, the
+// wavefronts share a chunk's sources in the scalar cache, which FP64's 22 KB (8 blocks) need more than FP32's 14 KB, but
+// wait for the slowest of each item.
 struct DrawPlan {
     int fixed_turns, in_step;
 };
-DrawPlan draw_plan(int nitems, unsigned grid, bool fp64) {
+DrawPlan draw_plan(int nitems, unsigned grid, int blk_per_chunk, bool fp64) {
     const int turns = nitems / (int)grid;
-    return DrawPlan{std::max(1, turns - 16), turns <= (fp64 ? 20 : 4)};
+    return DrawPlan{std::max(1, turns - 32), turns <= (fp64 || blk_per_chunk > 16 ? 20 : 4)};
 }
 
 // one operator application for all (or all unfinished) problems, src 0: V[k], 1: x;
@@ -715,7 +717,7 @@ void apply_all(BatchEngine* b, int prec, int src, int dst, int use_done, const i
     int32_t* next = b->next_item.as<int32_t>();
     auto sum = [&](auto real) {
         using Real = decltype(real);
-        const DrawPlan plan = draw_plan(b->nitems, grid, sizeof(Real) == 8);
+        const DrawPlan plan = draw_plan(b->nitems, grid, b->blk_per_chunk, sizeof(Real) == 8);
         b_lgf_sum<Real><<<grid, kSumThreads, 0, st>>>(P, b->items.as<Item>(), b->nitems, plan.fixed_turns, plan.in_step,
                                                       use_done, sel, next);
     };

@@ -37,7 +37,7 @@ def test_every_order_gives_the_same(members, blocks, grid, tmp_path, monkeypatch
     items = sum(-(-c.sizes["n_targets"] // 1024) * -(-(-(-c.sizes["n_sources"] // 64)) // blocks) for c in ctxs)
     print("items to a workgroup", items / (256 * grid), flush=True)
     if blocks == 1:
-        assert 65 * 256 < items < 78 * 256   # the last 16 turns cross the 64th, where slots are freed
+        assert 65 * 256 < items < 78 * 256   # the last 32 turns cross the 64th, where slots are freed
     with P.Batch(ctxs) as b:
         for use_graph in (False, True):
             b.solve(P.SOLVE_FP64, tol=1e-14, maxit=3, use_graph=use_graph)
